@@ -23,6 +23,10 @@
 //    stretch of row c).
 // The panels of super-block t therefore overlap the wide GEMM of super-block
 // t-1; after the last one a GEMM-only step leaves R = (What - W) Sigma exact.
+//
+// This blocked form runs the sweeps that move most coordinates (the first from
+// What = W, relaxed sweeps) and those of QE_CD_DENSE, QE_CD_FP32 and p > 16384;
+// the others run row by row (cd_rows.hip).
 #include <utility>
 
 #include "nt_x3.h"
@@ -31,31 +35,31 @@
 namespace qe {
 
 // ---------------------------------------------------------------- setup kernels
-__global__ void diag_prep_kernel(const float* __restrict__ Sigma, int64_t p, float* inv_d,
-                                 int* status)
+// inv_d = 1 / diag(Sigma), inv_s = 1 / scale, with their checks; `moving` (n ints,
+// or n = 0) starts at 0.
+__global__ void prep_kernel(const float* __restrict__ Sigma, int64_t p, float* inv_d,
+                            const float* __restrict__ scale, const float* __restrict__ zero,
+                            int64_t q, float* inv_s, int* moving, int n, int* status)
 {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= p) return;
-    const float d = Sigma[j * p + j];
-    if (!(d > 0.f) || !isfinite(d)) {
-        set_status(status, QE_ERR_DIAG);
-        inv_d[j] = 0.f;
-    } else {
-        inv_d[j] = 1.0f / d;
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n) moving[t] = 0;
+    if (t < p) {
+        const float d = Sigma[t * p + t];
+        if (!(d > 0.f) || !isfinite(d)) {
+            set_status(status, QE_ERR_DIAG);
+            inv_d[t] = 0.f;
+        } else {
+            inv_d[t] = 1.0f / d;
+        }
     }
-}
-
-__global__ void grid_prep_kernel(const float* __restrict__ scale, const float* __restrict__ zero,
-                                 int64_t q, float* inv_s, int* status)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= q) return;
-    const float s = scale[i], z = zero[i];
-    if (!(s > 0.f) || !isfinite(s) || !isfinite(z)) {
-        set_status(status, QE_ERR_SCALE);
-        inv_s[i] = 0.f;
-    } else {
-        inv_s[i] = 1.0f / s;
+    if (t < q) {
+        const float s = scale[t], z = zero[t];
+        if (!(s > 0.f) || !isfinite(s) || !isfinite(z)) {
+            set_status(status, QE_ERR_SCALE);
+            inv_s[t] = 0.f;
+        } else {
+            inv_s[t] = 1.0f / s;
+        }
     }
 }
 
@@ -153,9 +157,10 @@ __global__ __launch_bounds__(256) void obj_partial_kernel(const float* __restric
 // equal prev).
 __global__ __launch_bounds__(256) void sum_partials_kernel(const double* partial, int n,
                                                            const double* prev, double* out,
+                                                           const int* gate, int limit,
                                                            const int* status)
 {
-    if (failed(status)) return;
+    if (failed(status) || (gate && *gate <= limit)) return;
     __shared__ double sh[256];
     double acc = 0.0;
     for (int e = threadIdx.x; e < n; e += blockDim.x) acc += partial[e];
@@ -195,6 +200,8 @@ struct StepArgs {
     double* fpart;        // per panel wave: the objective change of this sweep's moves so far
     int fobj;             // accumulate fpart (the per-sweep objective is wanted)
     int ffirst;           // first launch of a sweep: fpart is written, not added to
+    const int* gate;      // optional sweep: runs only while *gate > limit (else null)
+    int limit;
     const int* status;
 };
 
@@ -1037,7 +1044,7 @@ constexpr int step_lds_floats()
 template <int SLOTS>
 __global__ __launch_bounds__(256, 2) void cd_step_kernel(StepArgs a)
 {
-    if (failed(a.status)) return;
+    if (failed(a.status) || (a.gate && *a.gate <= a.limit)) return;
     static_assert(step_lds_floats<SLOTS>() >= kLaCols * kLaStride, "look-ahead staging fits");
     __shared__ __attribute__((aligned(16))) float lds[step_lds_floats<SLOTS>()];
     if ((int)blockIdx.x < a.n_panel)
@@ -1047,6 +1054,17 @@ __global__ __launch_bounds__(256, 2) void cd_step_kernel(StepArgs a)
 }
 
 // ---------------------------------------------------------------- host side
+// A sweep from valid codes runs row by row (cd_rows.hip) when few coordinates
+// move.  That is known on the device only: for the first sweeps of a call both
+// forms are enqueued, and a count over a sample of rows, taken before the
+// sweep, decides which of them does the work.  From the fourth sweep from What =
+// W on the row form was the faster one on every layer measured, and each unused
+// blocked sweep costs about 85 us of empty launches (4096 columns), so the later
+// sweeps are not given the choice.
+constexpr int kMaxOptional = 4;          // sweeps 0 .. 3 of a call
+constexpr int kMovingWord = 16;          // their counts, in the status region
+static_assert((kMovingWord + kMaxOptional) * sizeof(int) <= kStatusBytes, "counts fit");
+
 static int block_width(int block) { return block == 0 ? 128 : block; }
 
 // Super-block width = the GEMM's K per launch (a multiple of the panel width).
@@ -1075,7 +1093,7 @@ qe_status launch_residual_dot(const float* W, const float* Wh, const float* H, c
     hipLaunchKernelGGL(obj_partial_kernel, dim3(kObjBlocks), dim3(256), 0, s, W, Wh, H, R, count,
                        vec4, part, status);
     hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, s, part, kObjBlocks,
-                       (const double*)nullptr, out, status);
+                       (const double*)nullptr, out, (const int*)nullptr, 0, status);
     return hipGetLastError() == hipSuccess ? QE_OK : QE_ERR_HIP;
 }
 
@@ -1111,7 +1129,7 @@ static qe_status launch_steps(StepArgs base, float* d0, float* d1, int* nz0, int
 qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, int bits,
                     const float* scale, const float* zero, float* Wh, uint8_t* codes, float* R,
                     const float* H, int sweeps, int block, uint32_t flags, double* obj,
-                    int obj_stride, const double* f_in, void* ws, hipStream_t s)
+                    int obj_stride, const double* f_in, int sweep0, void* ws, hipStream_t s)
 {
     const int B = block_width(block);
     const int S = super_width(B);
@@ -1138,10 +1156,9 @@ qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, in
             if (launch_nonfinite_scan(inputs[k], counts[k], status, s) != QE_OK) return QE_ERR_HIP;
         if (launch_nonfinite_scan(H, q * p, status, s) != QE_OK) return QE_ERR_HIP;
     }
-    hipLaunchKernelGGL(diag_prep_kernel, dim3((unsigned)cdiv(p, 256)), dim3(256), 0, s, Sigma, p,
-                       inv_d, status);
-    hipLaunchKernelGGL(grid_prep_kernel, dim3((unsigned)cdiv(q, 256)), dim3(256), 0, s, scale,
-                       zero, q, inv_s, status);
+    int* const moving = status + kMovingWord;
+    hipLaunchKernelGGL(prep_kernel, dim3((unsigned)cdiv(std::max(p, q), 256)), dim3(256), 0, s, Sigma, p,
+                       inv_d, scale, zero, q, inv_s, moving, sweep0 == 0 ? kMaxOptional : 0, status);
     const bool vec4 = aligned16(Sigma) && aligned16(W) && aligned16(Wh) && (p % 4 == 0) &&
                       (!H || aligned16(H));
     if (flags & QE_INIT_FROM_W) {
@@ -1187,6 +1204,11 @@ qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, in
     const bool codes_valid0 = (flags & QE_CODES_VALID) && !(flags & QE_INIT_FROM_W);
     const int period = (int)((flags & QE_RELAX_MASK) >> 8);
     bool prev_relaxed = false;
+    const double* const f0 = f_prev;
+    const bool rows = !base.dense && !base.fp32 && period == 0 && cd_rows_fits(p);
+    const int limit = rows ? cd_rows_limit(q, p) : -1;
+    const int max_optional = limit >= 0 ? kMaxOptional : 0;
+    int opt0 = -1;                       // first sweep from valid codes (with rows)
     for (int sw = 0; sw < sweeps; ++sw) {
         const int k = sw + 1;
         base.relax = (period > 0 && k % period == 0 && k != sweeps) ? 1 : 0;
@@ -1199,6 +1221,18 @@ qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, in
         // s (k - z) rather than their fp32 roundings.
         base.intd = (base.codes_valid && !base.relax) ? 1 : 0;
         prev_relaxed = base.relax != 0;
+        if (rows && base.intd) {
+            if (opt0 < 0) opt0 = sw;
+            if (sweep0 + sw >= max_optional) break;
+            // optional: these launches do nothing when few coordinates move
+            int* const cnt = moving + sweep0 + sw;
+            const bool before = sw > opt0 || (sw == 0 && sweep0 > 1);
+            if (launch_cd_sample(R, Wh, inv_d, scale, zero, inv_s, q, p, base.maxq,
+                                 before ? cnt - 1 : nullptr, limit, cnt, status, s) != QE_OK)
+                return QE_ERR_HIP;
+            base.gate = cnt;
+            base.limit = limit;
+        }
         qe_status st;
         switch (B) {
             case 16: st = launch_steps<1>(base, d0, d1, nz0, nz1, q, p, s); break;
@@ -1210,10 +1244,16 @@ qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, in
         if (obj) {
             double* out = obj + (size_t)sw * obj_stride;
             hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, s, fpart, n_fpart,
-                               f_prev, out, status);
+                               f_prev, out, base.gate, base.limit, status);
             if (hipGetLastError() != hipSuccess) return QE_ERR_HIP;
             f_prev = out;
         }
+    }
+    if (opt0 >= 0) {
+        const int opt1 = std::max(opt0, std::min(sweeps, max_optional - sweep0));
+        return launch_cd_rows(Sigma, q, p, inv_d, scale, zero, inv_s, base.maxq, Wh, codes, R, sweeps,
+                              moving + sweep0 + opt0, opt0, opt1, limit, obj, obj_stride, f0,
+                              reinterpret_cast<double*>(d0), q * S / 2, status, s);
     }
     return QE_OK;
 }

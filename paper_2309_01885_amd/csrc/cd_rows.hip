@@ -1,0 +1,372 @@
+// Sweeps from valid codes, one workgroup per row (gfx950).
+//
+// From the second sweep on most coordinates keep their level, and a kept
+// coordinate changes nothing: neither its code, nor R.  Rows are independent
+// (Sec. 3.2), so such a sweep is, for one row, a search for the next column
+// whose level moves, followed by that column's rank-1 update
+// R_i += delta Sigma_j over all p columns.  Its cost goes with the number of
+// moves instead of with p column steps and a q x p x p product.
+//
+// The row's residual stays in registers over all the sweeps of a launch: wave
+// w of the workgroup owns 256 G consecutive columns, lane l the columns
+// 256 g + 4 l .. + 3 of its groups g.  The waves take turns in column order.
+// The wave whose turn it is looks at one group of 256 columns at a time: every
+// lane decides its four coordinates, ballots give the first column that
+// moves, its update is applied to the wave's own columns, and the search goes
+// on behind that column.  The moves are listed in LDS; after the turn (one
+// barrier; two lists alternate, so that the next turn may write while slower
+// waves still read) the other waves apply the list to their columns.
+//
+// Bound: each move reads one row of Sigma, 4 p bytes.  At 4096 x 4096 and 5% moves
+// 858000 of them take 1.5 ms (9.4 TB/s, Sigma from the die-level cache), at 4096 x
+// 11008 (Sigma 485 MB, from HBM) 1.57 million take 9.9 ms (7 TB/s); below about
+// 0.1% the launch's own reads and writes of R, What and the codes remain (0.11
+// ms at 4096 x 4096, paid once per launch and not per sweep).  The blocked sweep
+// takes 0.4 to 1.1 ms there and 2.2 to 6.9 ms at 4096 x 11008.  Ten sweeps from
+// What = W: 8.1 -> 3.25 ms (4096 x 4096), 45.7 -> 19.8 ms (4096 x 11008), 26.3
+// -> 14.6 ms (11008 x 4096), 8.7 -> 2.6 ms (1003 x 3001).
+// 1024 columns per wave keep a lane's state (16 values of R, 16 codes) at 79
+// registers: six waves per SIMD, which hide the latency of the serial search of
+// one row behind the other rows.  Turns of 256 columns in place of 1024 (more
+// barriers, more reuse of Sigma rows in L2) took 10 to 30% longer, and 8 waves
+// of 1536 columns at p = 11008 (139 registers) 25% longer than 11 of 1024.
+#include <algorithm>
+
+#include "qe_internal.h"
+
+namespace qe {
+
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+struct RowsArgs {
+    const float* Sigma;
+    const float* inv_d;
+    const float* scale;
+    const float* zero;
+    const float* inv_s;
+    float* Wh;
+    uint8_t* codes;
+    float* R;
+    int64_t q, p;
+    float maxq;
+    int k0, k1;           // sweeps of the call that this launch may run
+    const int* moving;    // sampled counts of sweeps opt0 .. opt1 - 1 (see cd_sample_kernel)
+    int opt0, opt1, limit;
+    double* fpart;        // (k1 - k0) x q: objective change of each row and sweep (or null)
+    const int* status;
+};
+
+// The first sweep that runs here: the first optional one whose sample holds at
+// most `limit` moves, else the first that is not optional.
+__device__ __forceinline__ int first_sweep(const int* moving, int opt0, int opt1, int limit)
+{
+    int k = opt0;
+    while (k < opt1 && moving[k - opt0] > limit) ++k;
+    return k;
+}
+
+// Four consecutive floats; those at or past the end of the row read as 0.
+template <bool FULL>
+__device__ __forceinline__ f32x4 load4(const float* row, int c, int n)
+{
+    if (FULL || c + 4 <= n) return *reinterpret_cast<const f32x4u*>(row + c);
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+        if (c + e < n) v[e] = row[c + e];
+    return v;
+}
+
+// The wave's columns: L += delta Sigma_j.
+template <int G, bool FULL>
+__device__ __forceinline__ void apply_move(f32x4 (&L)[G], const float* srow, int c0, int n, float delta)
+{
+    f32x4 v[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) v[g] = load4<FULL>(srow, c0 + 256 * g, n);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) L[g][e] = fmaf(delta, v[g][e], L[g][e]);
+}
+
+// One turn: the wave's columns in order.  Returns the number of moves.
+template <int G, bool FULL>
+__device__ __forceinline__ int take_turn(const RowsArgs& a, f32x4 (&L)[G], uint32_t (&code)[G], int c0,
+                                         int wcol, float s, float inv_s, int2* list, double& f)
+{
+    const int lane = threadIdx.x & 63;
+    const int n = (int)a.p;
+    int cnt = 0;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        if (!FULL && wcol + 256 * g >= n) break;
+        f32x4 u = load4<FULL>(a.inv_d, c0 + 256 * g, n);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) u[e] *= inv_s;
+        // the columns still to be taken: inside the row, behind the last move
+        uint64_t open[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) open[e] = FULL ? ~0ull : __ballot(c0 + 256 * g + e < n);
+        for (;;) {
+            float d[4];
+            uint64_t m[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float kc = (float)((code[g] >> (8 * e)) & 0xffu);
+                // Lemma 1's minimiser on the grid axis, its nearest level; a valid,
+                // equally near current level is kept (Sec. 3.3)
+                const float t = fmaf(-L[g][e], u[e], kc);
+                const float kn = __builtin_amdgcn_fmed3f(rintf(t), 0.f, a.maxq);
+                d[e] = kn - kc;
+                m[e] = __ballot(d[e] != 0.f && !(fabsf(t - kc) <= fabsf(t - kn))) & open[e];
+            }
+            const uint64_t any = m[0] | m[1] | m[2] | m[3];
+            if (any == 0) break;
+            const int ls = __builtin_ctzll(any);
+            const int es = (m[0] >> ls) & 1 ? 0 : (m[1] >> ls) & 1 ? 1 : (m[2] >> ls) & 1 ? 2 : 3;
+            const float dsel = es == 0 ? d[0] : es == 1 ? d[1] : es == 2 ? d[2] : d[3];
+            const float dm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(dsel), ls));
+            const float delta = s * dm;
+            const int j = wcol + 256 * g + 4 * ls + es;
+            const uint64_t behind = (~0ull << ls) << 1;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) open[e] &= behind | (e > es ? 1ull << ls : 0ull);
+            if (list && lane == 0) list[cnt] = make_int2(j, __float_as_int(delta));
+            const float r0 = es == 0 ? L[g][0] : es == 1 ? L[g][1] : es == 2 ? L[g][2] : L[g][3];
+            apply_move<G, FULL>(L, a.Sigma + (int64_t)j * a.p, c0, n, delta);
+            const float r1 = es == 0 ? L[g][0] : es == 1 ? L[g][1] : es == 2 ? L[g][2] : L[g][3];
+            if (lane == ls) {
+                code[g] += (uint32_t)((int)dm << (8 * es));
+                // the move changes f by delta (2 R + delta Sigma_jj) = delta (R + R')
+                f += (double)delta * ((double)r0 + (double)r1);
+            }
+            ++cnt;
+        }
+    }
+    return cnt;
+}
+
+// MULTI: several waves per row, 1024 columns each; else one wave.
+template <int G, bool MULTI>
+__global__ __launch_bounds__(MULTI ? 1024 : 64) void cd_rows_kernel(RowsArgs a)
+{
+    if (failed(a.status)) return;
+    const int start = max(a.k0, first_sweep(a.moving, a.opt0, a.opt1, a.limit));
+    if (start >= a.k1) return;
+    __shared__ int2 list[2][MULTI ? 256 * G : 1];
+    __shared__ int count[2];
+    __shared__ double fw[16];
+    const int W = MULTI ? (int)blockDim.x >> 6 : 1;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t i = blockIdx.x;
+    const int n = (int)a.p;
+    const int wcol = 256 * G * wave;
+    const int c0 = wcol + 4 * lane;
+    const bool full = wcol + 256 * G <= n;
+    const float s = a.scale[i], z = a.zero[i], inv_s = a.inv_s[i];
+    float* Rrow = a.R + i * a.p;
+    float* Wrow = a.Wh + i * a.p;
+    uint8_t* crow = a.codes + i * a.p;
+    f32x4 L[G];
+    uint32_t code[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        L[g] = load4<false>(Rrow, c0 + 256 * g, n);
+        const f32x4 w = load4<false>(Wrow, c0 + 256 * g, n);
+        // the current code is recovered exactly from What (|k - z| <= 255 keeps
+        // the rounding error far below 1/2)
+        code[g] = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (c0 + 256 * g + e < n)
+                code[g] |= (uint32_t)__builtin_amdgcn_fmed3f(rintf(fmaf(w[e], inv_s, z)), 0.f, 255.f)
+                           << (8 * e);
+    }
+    int turn = 0;
+    for (int sw = start; sw < a.k1; ++sw) {
+        double f = 0.0;
+        int moves = 0;
+        for (int w = 0; w < W; ++w, turn ^= 1) {
+            int2* li = MULTI ? list[turn] : nullptr;
+            if (wave == w) {
+                const int cnt = full ? take_turn<G, true>(a, L, code, c0, wcol, s, inv_s, li, f)
+                                     : take_turn<G, false>(a, L, code, c0, wcol, s, inv_s, li, f);
+                if (lane == 0) count[turn] = cnt;
+            }
+            __syncthreads();
+            const int cnt = count[turn];
+            moves += cnt;
+            if (wave != w) {
+                if (full) {
+                    for (int k = 0; k < cnt; ++k) {
+                        const int2 en = li[k];
+                        const int j = __builtin_amdgcn_readfirstlane(en.x);
+                        apply_move<G, true>(L, a.Sigma + (int64_t)j * a.p, c0, n, __int_as_float(en.y));
+                    }
+                } else if (wcol < n) {
+                    for (int k = 0; k < cnt; ++k) {
+                        const int2 en = li[k];
+                        const int j = __builtin_amdgcn_readfirstlane(en.x);
+                        apply_move<G, false>(L, a.Sigma + (int64_t)j * a.p, c0, n, __int_as_float(en.y));
+                    }
+                }
+            }
+        }
+        if (a.fpart) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) f += __shfl_xor(f, o, 64);
+            if (lane == 0) fw[wave] = f;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                double t = 0.0;
+                for (int w = 0; w < W; ++w) t += fw[w];
+                a.fpart[(int64_t)(sw - a.k0) * a.q + i] = t;
+            }
+        }
+        if (moves == 0) {       // a fixed point: no later sweep moves anything
+            if (a.fpart && threadIdx.x == 0)
+                for (int k = sw + 1; k < a.k1; ++k) a.fpart[(int64_t)(k - a.k0) * a.q + i] = 0.0;
+            break;
+        }
+    }
+    const bool words = (n & 3) == 0 && (reinterpret_cast<uintptr_t>(a.codes) & 3) == 0;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const int c = c0 + 256 * g;
+        f32x4 w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = s * ((float)((code[g] >> (8 * e)) & 0xffu) - z);
+        if (c + 4 <= n) {
+            *reinterpret_cast<f32x4u*>(Rrow + c) = L[g];
+            *reinterpret_cast<f32x4u*>(Wrow + c) = w;
+            if (words) {
+                *reinterpret_cast<uint32_t*>(crow + c) = code[g];
+                continue;
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (c + e < n) {
+                Rrow[c + e] = L[g][e];
+                Wrow[c + e] = w[e];
+                crow[c + e] = (uint8_t)(code[g] >> (8 * e));
+            }
+    }
+}
+
+// obj[k] = the objective before sweep k + its change, for the sweeps of a
+// cd_rows_kernel launch; each sweep's changes are summed over the rows in a fixed
+// order.  f0: the objective before the call's first sweep (null: 0).
+__global__ __launch_bounds__(256) void rows_objective_kernel(RowsArgs a, const double* f0, double* obj,
+                                                             int stride)
+{
+    if (failed(a.status)) return;
+    const int start = max(a.k0, first_sweep(a.moving, a.opt0, a.opt1, a.limit));
+    if (start >= a.k1) return;
+    __shared__ double sh[256];
+    double f = start > 0 ? obj[(int64_t)(start - 1) * stride] : (f0 ? *f0 : 0.0);
+    for (int k = start; k < a.k1; ++k) {
+        const double* part = a.fpart + (int64_t)(k - a.k0) * a.q;
+        double acc = 0.0;
+        for (int64_t e = threadIdx.x; e < a.q; e += blockDim.x) acc += part[e];
+        f += block_sum_f64(acc, sh);
+        if (threadIdx.x == 0) obj[(int64_t)k * stride] = f;
+    }
+}
+
+// How many coordinates of a sample of rows (every q / gridDim.x-th) would move
+// from the present state, into *moving (zeroed before).  `prev` (or null): the
+// count of the sweep before; once a sweep has run row by row, so do the later
+// ones, and theirs stays 0.
+__global__ __launch_bounds__(256) void cd_sample_kernel(const float* __restrict__ R,
+                                                        const float* __restrict__ Wh,
+                                                        const float* __restrict__ inv_d,
+                                                        const float* __restrict__ scale,
+                                                        const float* __restrict__ zero,
+                                                        const float* __restrict__ inv_s, int64_t q,
+                                                        int64_t p, float maxq, const int* prev, int limit,
+                                                        int* moving, const int* status)
+{
+    if (failed(status)) return;
+    if (prev && *prev <= limit) return;
+    const int64_t i = (int64_t)blockIdx.x * q / gridDim.x;
+    const float z = zero[i], is = inv_s[i];
+    int n = 0;
+#pragma unroll 4
+    for (int64_t j = threadIdx.x; j < p; j += blockDim.x) {
+        const float kc = rintf(fmaf(Wh[i * p + j], is, z));
+        const float t = fmaf(-R[i * p + j], inv_d[j] * is, kc);
+        const float kn = __builtin_amdgcn_fmed3f(rintf(t), 0.f, maxq);
+        n += kn != kc && !(fabsf(t - kc) <= fabsf(t - kn));
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
+    if ((threadIdx.x & 63) == 0 && n) atomicAdd(moving, n);
+}
+
+constexpr int64_t kRowsMaxP = 16384;     // 16 waves of 1024 columns
+constexpr int kSampleRows = 256;
+
+bool cd_rows_fits(int64_t p) { return p <= kRowsMaxP; }
+
+// The most moves in the sample with which the row form is taken, or -1: always.
+// The row form costs 4 p bytes per move, at 9 TB/s while Sigma fits the die-level
+// cache and 7 TB/s beyond; the blocked form its products, at 135 TFLOP/s (fp32
+// products; 125 to 144 measured over 4096 x 4096, 11008 x 4096 and 4096 x 11008),
+// or the column steps of its launches, 50 us for 256 columns, where rows are few.
+// The line lies where the two are equal: 3.3% at 4096 x 4096 (measured: 5.1%,
+// 1.60 against 1.13 ms; 0.9%, 0.38 against 1.06 ms), 2.6% at 4096 x 11008 (3.5%,
+// 9.9 against 6.9 ms; 0.7%, 2.3 against 6.6 ms).  Above 12% no layer of so few
+// rows is worth the blocked launches (1003 x 3001, 5%: 0.36 against 0.91 ms).
+// Strongly coupled channels move less than the sample says (the first move
+// settles its neighbours): the blocked form is then kept a few sweeps longer.
+
+int cd_rows_limit(int64_t q, int64_t p)
+{
+    const double work = (double)q * (double)p * (double)p;
+    const double bw = 4.0 * (double)p * (double)p <= 2.0e8 ? 9.0e12 : 7.0e12;
+    const double dense = std::max(2.0 * work / 135.0e12, (double)(cdiv(p, 256) + 1) * 50.0e-6);
+    const double f = dense * bw / (4.0 * work);
+    if (f > 0.12) return -1;
+    return (int)(f * (double)std::min<int64_t>(q, kSampleRows) * (double)p);
+}
+
+qe_status launch_cd_sample(const float* R, const float* Wh, const float* inv_d, const float* scale,
+                           const float* zero, const float* inv_s, int64_t q, int64_t p, float maxq,
+                           const int* prev, int limit, int* moving, const int* status, hipStream_t s)
+{
+    hipLaunchKernelGGL(cd_sample_kernel, dim3((unsigned)std::min<int64_t>(q, kSampleRows)), dim3(256), 0,
+                       s, R, Wh, inv_d, scale, zero, inv_s, q, p, maxq, prev, limit, moving, status);
+    return hipGetLastError() == hipSuccess ? QE_OK : QE_ERR_HIP;
+}
+
+// Sweeps [opt0, sweeps) of a call, of which [opt0, opt1) are optional.  fpart:
+// room for fpart_count doubles (at least one sweep of q).
+qe_status launch_cd_rows(const float* Sigma, int64_t q, int64_t p, const float* inv_d, const float* scale,
+                         const float* zero, const float* inv_s, float maxq, float* Wh, uint8_t* codes,
+                         float* R, int sweeps, const int* moving, int opt0, int opt1, int limit, double* obj,
+                         int obj_stride, const double* f0, double* fpart, int64_t fpart_count,
+                         const int* status, hipStream_t s)
+{
+    const int per = obj ? (int)std::max<int64_t>(1, std::min<int64_t>(sweeps, fpart_count / q)) : sweeps;
+    for (int k = opt0; k < sweeps; k += per) {
+        RowsArgs a{Sigma, inv_d, scale, zero, inv_s, Wh, codes, R, q, p, maxq, k, std::min(k + per, sweeps),
+                   moving, opt0, opt1, limit, obj ? fpart : nullptr, status};
+        const dim3 grid((unsigned)q);
+#define QE_ROWS(G, M) \
+    hipLaunchKernelGGL((cd_rows_kernel<G, M>), grid, dim3((unsigned)(64 * cdiv(p, 256 * G))), 0, s, a)
+        if (p <= 256) QE_ROWS(1, false);
+        else if (p <= 512) QE_ROWS(2, false);
+        else if (p <= 1024) QE_ROWS(4, false);
+        else QE_ROWS(4, true);
+#undef QE_ROWS
+        if (obj)
+            hipLaunchKernelGGL(rows_objective_kernel, dim3(1), dim3(256), 0, s, a, f0, obj, obj_stride);
+        if (hipGetLastError() != hipSuccess) return QE_ERR_HIP;
+    }
+    return QE_OK;
+}
+
+}  // namespace qe

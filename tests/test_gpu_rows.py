@@ -1,0 +1,77 @@
+"""Sweeps from valid codes run row by row (Sec. 3.2: rows are independent; a
+kept coordinate changes nothing), against the fp64 oracle through the parity
+protocol of tests/parity.py, at the edges of the kernel's column groups (256),
+of one wave's columns (1024) and of its range (16384), and where the choice
+between this form and the blocked one is made on the device."""
+import numpy as np
+import pytest
+
+import synth
+from parity import dev, host, teacher_forced
+from test_gpu_cd import check_parity, gpu_cd, layer
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("q,p,bits", [(3, 1, 4), (7, 3, 3), (5, 255, 4), (5, 256, 8), (5, 257, 3),
+                                      (6, 512, 2), (6, 513, 4), (4, 1023, 3), (4, 1025, 4),
+                                      (3, 2048, 1), (3, 4099, 3), (2, 16384, 4)])
+def test_rows_match_oracle(qe, oracle, q, p, bits):
+    W, X = layer(q, p, 64 if p > 8192 else 2 * p + 64, 51 + p, corr=0.5)
+    # few tokens: more damping keeps the conditioning of the longer runs
+    S32 = oracle.damp(oracle.gram(X), 4.0 if p > 8192 else 0.01).astype(np.float32)
+    scale, zero = oracle.grid_minmax(W, bits)
+    g = gpu_cd(qe, W, S32, bits, scale, zero, 3)
+    check_parity(oracle, W, S32, bits, scale, zero, g, f"rows {q}x{p} b={bits}")
+    one = gpu_cd(qe, W, S32, bits, scale, zero, 3, per_sweep=False)
+    for k in ("What", "codes", "R"):
+        assert np.array_equal(one[k], g[k])
+    assert one["obj"] == g["obj"]
+
+
+def test_choice_on_the_device(qe, oracle):
+    """2048 x 2048 with few tokens: more coordinates would move in sweep 2 than
+    the row form is given (blocked sweep), fewer in the later ones (rows)."""
+    q = p = 2048
+    W, X = layer(q, p, 1024, 52)
+    S32 = oracle.damp(oracle.gram(X), 0.01).astype(np.float32)
+    scale, zero = oracle.grid_minmax(W, 4)
+    g = gpu_cd(qe, W, S32, 4, scale, zero, 5)
+    one = gpu_cd(qe, W, S32, 4, scale, zero, 5, per_sweep=False)
+    for k in ("What", "codes", "R"):
+        assert np.array_equal(one[k], g[k])
+    assert one["obj"] == g["obj"]
+    # R rounds as in the blocked form exactly while the blocked form ran
+    dense = gpu_cd(qe, W, S32, 4, scale, zero, 5, extra=qe.QE_CD_DENSE)
+    same = [np.array_equal(a, b) for a, b in zip(g["Rs"], dense["Rs"])]
+
+    def would_move(k):
+        t = np.rint(g["whats"][k] / scale[:, None] + zero[:, None])
+        u = t - g["Rs"][k] / np.diag(S32) / scale[:, None]
+        return float(np.mean(np.clip(np.rint(u), 0, 15) != t))
+
+    assert would_move(0) > 0.13 and would_move(1) < 0.1      # the line lies at 0.118 here
+    assert same[0] and same[1] and not same[4], same
+    rows = synth.row_sample(q, 48, 2)
+    cut = lambda hist: [h[rows] for h in hist]
+    teacher_forced(oracle, W[rows], S32.astype(np.float64), 4, scale[rows], zero[rows], cut(g["hist"]),
+                   cut(g["whats"]), cut(g["Rs"]), label="choice 2048x2048")
+
+
+def test_fixed_point_and_no_objective(qe, oracle):
+    """Rows that stop moving leave the later sweeps early: the objective stays,
+    and a call without one gives the same state."""
+    W, X = layer(40, 300, 2048, 53, corr=0.5)
+    S32 = oracle.damp(oracle.gram(X), 0.01).astype(np.float32)
+    scale, zero = oracle.grid_minmax(W, 4)
+    g = gpu_cd(qe, W, S32, 4, scale, zero, 60, per_sweep=False)
+    assert g["obj"][-1] == g["obj"][-2] == g["obj"][40]
+    assert all(a >= b for a, b in zip(g["obj"], g["obj"][1:]))
+    Wd, Sd, sc, ze = dev(W), dev(S32), dev(scale), dev(zero)
+    Wh, R, codes = dev(W), dev(W), dev(np.zeros(W.shape, np.uint8))
+    qe.cd_sweep(Wd, Sd, 4, sc, ze, Wh, codes, R, 60)
+    assert np.array_equal(host(Wh), g["What"]) and np.array_equal(host(R), g["R"])
+    assert np.array_equal(host(codes), g["codes"])
+    before = host(R).copy()
+    qe.cd_sweep(Wd, Sd, 4, sc, ze, Wh, codes, R, 2, flags=qe.QE_R_VALID | qe.QE_CODES_VALID)
+    assert np.array_equal(host(R), before) and np.array_equal(host(codes), g["codes"])
