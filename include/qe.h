@@ -116,9 +116,8 @@ qe_status qe_sync_status(void* ws, void* stream);
  * Sigma: p x p fp32, device; overwritten (accumulate = 0) or added to
  * (accumulate = 1, for token chunks streamed through several calls; pass
  * damp = 0 on all but the last).  The result is exactly symmetric.
- * Products, by default: when p is a multiple of 256 (at most 2^24), X's rows
- * are 16-byte aligned, n is a multiple of 32 (token-major X: all but its last
- * n % 32 tokens) and either the split partials fit the workspace or
+ * Products, by default: when p is a multiple of 256 or p p n is at least 3e9 (p at
+ * most 2^24) and either the split partials fit the workspace or
  * n <= 32768 (at very large p, stream longer token ranges in chunks of at
  * most 32768), each channel i is first scaled by 2^e_i (exact; its largest |x|
  * lands in [2^14, 2^15), a pass over X; e_i at most 127) and each scaled value

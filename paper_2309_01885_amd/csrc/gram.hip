@@ -281,7 +281,13 @@ __device__ inline void band_index_wide(int64_t t, int64_t nt, int64_t& ti, int64
 // F2: the two-way fp16 split of nt_f2.h, channel i scaled by 2^chexp[i] on the
 // way in and every sum scaled back by 2^-(chexp[i] + chexp[j]) on the way out
 // (exact); otherwise the three-way bf16 split of nt_x3.h (chexp unused).
-template <bool DIRECT, bool TRANS, bool F2>
+//
+// EDGE (F2 only): p is no multiple of 256, or token counts are none of 32, or
+// channel-major rows are not 16-byte aligned.  The tiles then reach past p;
+// channels there take some other channel's values (in bounds), their sums are
+// not stored, and tokens past the end read as 0.  Token-major loads guard
+// themselves through their descriptor in either case.
+template <bool DIRECT, bool TRANS, bool F2, bool EDGE>
 __global__ __launch_bounds__(512, 1) void gram_x3w_kernel(
     const float* __restrict__ X, int64_t p, int64_t n, int64_t ntw, int64_t tiles_w, int64_t nt,
     int64_t tiles, int64_t splits, int64_t split_len, float* __restrict__ out, int accumulate,
@@ -299,7 +305,10 @@ __global__ __launch_bounds__(512, 1) void gram_x3w_kernel(
     int64_t ti, tj;
     band_index_wide(item % tiles_w, ntw, ti, tj);
     const int64_t k0 = sp * split_len;
-    const int64_t K = min(n, k0 + split_len) - k0;
+    const int64_t kv = min(n, k0 + split_len) - k0;
+    const int64_t K = EDGE ? cdiv(kv, 2 * kX3KC) * (2 * kX3KC) : kv;
+    // exponent of channel c (EDGE: those past the end repeat the last one)
+    auto cexp = [&](int64_t c) { return chexp[EDGE ? min(c, p - 1) : c]; };
     f32x16 acc[2][4];
 #pragma unroll
     for (int mi = 0; mi < 2; ++mi)
@@ -311,9 +320,16 @@ __global__ __launch_bounds__(512, 1) void gram_x3w_kernel(
         // X is n x p; this thread stages channel t / 2 of both panels (eight
         // tokens, buffer loads); four stage buffers
         const int r = threadIdx.x >> 1;
-        const F2ColB A{X + k0 * p, p, ldexpf(1.f, chexp[ti * kWide + r])};
-        const F2ColB B{X + k0 * p, p, ldexpf(1.f, chexp[tj * kWide + r])};
+        const F2ColB<EDGE> A{X + k0 * p, p, ldexpf(1.f, cexp(ti * kWide + r)), kv};
+        const F2ColB<EDGE> B{X + k0 * p, p, ldexpf(1.f, cexp(tj * kWide + r)), kv};
         nt_tile_f2_wide<4>(A, ti * kWide, B, tj * kWide, K, lds, acc);
+    } else if constexpr (F2 && EDGE) {
+        const int r = threadIdx.x >> 2;
+        const F2RowQE A{{X + k0, n, {ldexpf(1.f, cexp(ti * kWide + r)),
+                                     ldexpf(1.f, cexp(ti * kWide + r + 128))}}, p, kv};
+        const F2RowQE B{{X + k0, n, {ldexpf(1.f, cexp(tj * kWide + r)),
+                                     ldexpf(1.f, cexp(tj * kWide + r + 128))}}, p, kv};
+        nt_tile_f2_wide<3>(A, ti * kWide, B, tj * kWide, K, lds, acc);
     } else if constexpr (F2) {
         // this thread stages channels t / 4 and t / 4 + 128 of both panels
         // (four tokens each); three stage buffers, which keep the loop free of
@@ -341,12 +357,12 @@ __global__ __launch_bounds__(512, 1) void gram_x3w_kernel(
     if constexpr (F2) {
         int ec[4];
 #pragma unroll
-        for (int ni = 0; ni < 4; ++ni) ec[ni] = chexp[tj * kWide + wn * 128 + 32 * ni + (lane & 31)];
+        for (int ni = 0; ni < 4; ++ni) ec[ni] = cexp(tj * kWide + wn * 128 + 32 * ni + (lane & 31));
 #pragma unroll
         for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int er = chexp[ti * kWide + wm * 64 + 32 * mi + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)];
+                const int er = cexp(ti * kWide + wm * 64 + 32 * mi + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3));
 #pragma unroll
                 for (int ni = 0; ni < 4; ++ni) acc[mi][ni][v] = ldexpf(acc[mi][ni][v], -(er + ec[ni]));
             }
@@ -358,7 +374,7 @@ __global__ __launch_bounds__(512, 1) void gram_x3w_kernel(
         for (int quad = 0; quad < 4; ++quad) {
             const int a = quad >> 1, b = quad & 1;          // rows 128 a.., columns 128 b..
             const int64_t gi = 2 * ti + a, gj = 2 * tj + b;
-            if (gi > gj) continue;                           // uniform across the workgroup
+            if (gi > gj || (EDGE && gj >= nt)) continue;     // uniform across the workgroup
             if (wm / 2 == a && wn == b) {
 #pragma unroll
                 for (int mi = 0; mi < 2; ++mi)
@@ -375,7 +391,8 @@ __global__ __launch_bounds__(512, 1) void gram_x3w_kernel(
         }
         return;
     }
-    if (qi > qj) return;                          // below the diagonal of a diagonal tile
+    // below the diagonal of a diagonal tile, or past the last 128 channels
+    if (qi > qj || (EDGE && qj >= nt)) return;
     float* dst = out + (sp * tiles + tri_row_start(qi, nt) + (qj - qi)) * kTileFloats;
 #pragma unroll
     for (int mi = 0; mi < 2; ++mi)
@@ -388,29 +405,31 @@ __global__ __launch_bounds__(512, 1) void gram_x3w_kernel(
 }
 
 // Adds the split partial tiles in fixed split order (fp64) and writes Sigma.
-// Workgroup (tile, quarter): rows [32 quarter, 32 quarter + 32) of the tile,
-// one float4 column group per thread and pass, all splits in flight.
-constexpr int kFinRows = 32;
-
+// Workgroup (tile, y): rows [ROWS y, ROWS (y + 1)) of the tile, one float4 column
+// group per thread and pass, eight splits in flight.  ROWS = 32 keeps the
+// mirrored writes in whole 128-byte lines; few tiles (small p, many splits) take
+// ROWS = 8 for four times the workgroups and a quarter of the serial loads: 512
+// channels x 64 splits 18.4 us with ROWS = 32 and four splits in flight.
+template <int ROWS>
 __global__ __launch_bounds__(256) void gram_finalize_kernel(const float* __restrict__ parts,
                                                             int64_t ntiles, int splits,
                                                             int64_t nt, float* Sigma, int64_t p,
                                                             int accumulate, const int* status)
 {
     if (failed(status)) return;
-    __shared__ float tl[kFinRows * kTStride];
+    __shared__ float tl[ROWS * kTStride];
     int64_t ti, tj;
     tri_index(blockIdx.x, nt, ti, tj);
-    const int r0 = (int)blockIdx.y * kFinRows;
+    const int r0 = (int)blockIdx.y * ROWS;
     const float* src0 = parts + (int64_t)blockIdx.x * kTileFloats + r0 * kTile;
     const int64_t sstride = ntiles * kTileFloats;
 #pragma unroll
-    for (int u = 0; u < kFinRows * kTile / 4 / 256; ++u) {
+    for (int u = 0; u < ROWS * kTile / 4 / 256; ++u) {
         const int f = threadIdx.x + 256 * u;
         const int r = f / (kTile / 4), c = 4 * (f % (kTile / 4));
         const float* src = src0 + r * kTile + c;
         double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-#pragma unroll 4
+#pragma unroll 8
         for (int sp = 0; sp < splits; ++sp) {
             const f32x4 v = *reinterpret_cast<const f32x4*>(src + sp * sstride);
             s0 += (double)v[0];
@@ -425,7 +444,7 @@ __global__ __launch_bounds__(256) void gram_finalize_kernel(const float* __restr
         d[3] = (float)s3;
     }
     __syncthreads();
-    write_symmetric(tl, ti, tj, Sigma, p, accumulate, r0, kFinRows);
+    write_symmetric(tl, ti, tj, Sigma, p, accumulate, r0, ROWS);
 }
 
 // Sigma_jj += damp * mean_j(Sigma_jj): one workgroup, fp64 mean.
@@ -482,61 +501,73 @@ __global__ __launch_bounds__(256) void chan_exp_pn_kernel(const float* __restric
     if (threadIdx.x == 0) chexp[blockIdx.x] = chan_exp(fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3])));
 }
 
-// Token-major X (n x p): workgroup (column block of 1024, token slice y) takes
-// the tokens y, y + slices, ... of its columns (4 per thread) and writes
-// their largest |x| to part[y * p + column]; chan_exp_np_kernel reduces.
+// Token-major X (n x p): workgroup (column block of 256, token slice y), lane l of
+// each wave four columns; wave w takes the tokens 4 y + w, 4 (y + slices) + w, ...
+// and the waves' largest |x| go to part[y * p + column]; chan_exp_np_kernel
+// reduces over the slices.  Rows need no alignment beyond their four bytes.
 __global__ __launch_bounds__(256) void chan_absmax_np_kernel(const float* __restrict__ X, int64_t p,
-                                                             int64_t n, int x_vec4,
-                                                             float* __restrict__ part,
+                                                             int64_t n, float* __restrict__ part,
                                                              const int* status)
 {
     if (failed(status)) return;
-    const int64_t c = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (c >= p) return;
-    const int64_t slices = gridDim.y;
-    f32x4 m = {0.f, 0.f, 0.f, 0.f};
-    if (x_vec4) {
-        // p % 4 == 0 and 16-byte aligned token rows: the 4 columns are inside X
-        float a = 0.f, b = 0.f, cc = 0.f, d = 0.f;
+    __shared__ f32x4 sh[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t c = (int64_t)blockIdx.x * 256 + 4 * lane;
+    const int64_t step = 4 * (int64_t)gridDim.y;
+    float m[4] = {0.f, 0.f, 0.f, 0.f};
+    if (c + 4 <= p) {
 #pragma unroll 8
-        for (int64_t t = blockIdx.y; t < n; t += slices) {
-            const f32x4 v = *reinterpret_cast<const f32x4*>(X + t * p + c);
-            a = fmaxf(a, fabsf(v[0]));
-            b = fmaxf(b, fabsf(v[1]));
-            cc = fmaxf(cc, fabsf(v[2]));
-            d = fmaxf(d, fabsf(v[3]));
-        }
-        m = f32x4{a, b, cc, d};
-    } else {
-        for (int64_t t = blockIdx.y; t < n; t += slices)
+        for (int64_t t = 4 * (int64_t)blockIdx.y + wave; t < n; t += step) {
+            const f32x4 v = *reinterpret_cast<const f32x4a4*>(X + t * p + c);
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < 4; ++u) m[u] = fmaxf(m[u], fabsf(v[u]));
+        }
+    } else if (c < p) {
+        for (int64_t t = 4 * (int64_t)blockIdx.y + wave; t < n; t += step)
+#pragma unroll
+            for (int u = 0; u < 3; ++u)
                 if (c + u < p) m[u] = fmaxf(m[u], fabsf(X[t * p + c + u]));
     }
+    sh[wave][lane] = f32x4{m[0], m[1], m[2], m[3]};
+    __syncthreads();
+    const int k = threadIdx.x;                         // channel of the block
+    const int64_t cc = (int64_t)blockIdx.x * 256 + k;
+    if (cc >= p) return;
+    float best = 0.f;
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-        if (c + u < p) part[blockIdx.y * p + c + u] = m[u];
+    for (int w = 0; w < 4; ++w) best = fmaxf(best, sh[w][k >> 2][k & 3]);
+    part[blockIdx.y * p + cc] = best;
 }
 
+// Workgroup: 64 channels, wave w every fourth slice.
 __global__ __launch_bounds__(256) void chan_exp_np_kernel(const float* __restrict__ part, int64_t p,
                                                           int slices, int* __restrict__ chexp,
                                                           const int* status)
 {
     if (failed(status)) return;
-    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (j >= p) return;
+    __shared__ float sh[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t j = (int64_t)blockIdx.x * 64 + lane;
     float m = 0.f;
+    if (j < p) {
 #pragma unroll 8
-    for (int y = 0; y < slices; ++y) m = fmaxf(m, part[y * p + j]);
-    chexp[j] = chan_exp(m);
+        for (int y = wave; y < slices; y += 4) m = fmaxf(m, part[y * p + j]);
+    }
+    sh[wave][lane] = m;
+    __syncthreads();
+    if (wave == 0 && j < p)
+        chexp[j] = chan_exp(fmaxf(fmaxf(sh[0][lane], sh[1][lane]), fmaxf(sh[2][lane], sh[3][lane])));
 }
 
-// Token slices of chan_absmax_np_kernel: about 2048 workgroups, at least 256
-// tokens a slice, at most 512 slices (the partials then hold at most 8 MB).
+// Token slices of chan_absmax_np_kernel: about 2048 workgroups, at most 512 slices
+// (the partials then hold at most 8 MB), and at least 256 tokens a slice, or 64
+// where that leaves fewer than 256 workgroups.
 static int64_t chan_slices(int64_t p, int64_t n)
 {
+    const int64_t blocks = cdiv(p, 256);
+    const int64_t few = std::min(cdiv(n, 64), cdiv(256, blocks));
     return std::max<int64_t>(
-        1, std::min<int64_t>(std::min<int64_t>(512, 2048 / cdiv(p, 1024)), cdiv(n, 256)));
+        1, std::min<int64_t>(std::min<int64_t>(512, 2048 / blocks), std::max(cdiv(n, 256), few)));
 }
 
 // Workspace of the channel exponents: p ints and the token-major partials.
@@ -555,17 +586,17 @@ static size_t chan_ws_bytes(int64_t p, int64_t n)
 // minimises, in units of one workgroup's time per token, rounds x (tokens per
 // split + a fixed cost per workgroup) + the finalize's reads of the partials,
 // over the counts whose splits hold at most kSplitTokensMax tokens and whose
-// partials fit kSplitBudget; ties keep the fewer splits.  Depends only on (p, n).
+// partials fit kSplitBudget; ties keep the fewer splits.
 constexpr int64_t kGramSlotsWide = 256, kGramSlotsNarrow = 512;
 constexpr double kGramWgCostTokens = 32.0;        // prologue, pipeline fill, partial-tile store
 constexpr double kGramFinalizeTokensPerTile = 0.11;   // one 64 KB partial tile read in finalize
 
-static int64_t gram_splits(int64_t p, int64_t n)
+static int64_t gram_splits(int64_t p, int64_t n, bool wide)
 {
     const int64_t nt = cdiv(p, kTile);
     const int64_t tiles = nt * (nt + 1) / 2;
-    const bool wide = p % kWide == 0;
-    const int64_t items = wide ? (p / kWide) * (p / kWide + 1) / 2 : tiles;
+    const int64_t ntw = cdiv(p, kWide);
+    const int64_t items = wide ? ntw * (ntw + 1) / 2 : tiles;
     const int64_t slots = wide ? kGramSlotsWide : kGramSlotsNarrow;
     const int64_t s_min = cdiv(n, kSplitTokensMax);
     const int64_t s_max = std::min<int64_t>(
@@ -586,17 +617,34 @@ static int64_t gram_splits(int64_t p, int64_t n)
     return best;
 }
 
+// The fp16 split on the 256 x 256 tiles takes every shape of enough work, whatever
+// p's remainder, the token count's and the rows' alignment: 4544 channels x 16383
+// tokens, token-major, 3.82 ms on the guarded 128 x 128 tiles of the bf16 split,
+// 1.31 ms here.  Below about 3e9 products (and p no multiple of 256) the pass for
+// the channel scales and the padding cost more than they give (995 x 826,
+// token-major: 38 us on the 128 x 128 tiles, 49 us here; 1100 x 5200: 116 and 75 us).
+static bool f2_applies(int64_t p, int64_t n, int layout)
+{
+    // (the token-major loader's buffer offsets are 32-bit)
+    return (layout & (QE_GRAM_FP32 | QE_GRAM_BF16X3)) == 0 && p <= (int64_t(1) << 24) &&
+           (p % kWide == 0 || (p > kTile && (double)p * (double)p * (double)n >= 3e9));
+}
+
+static bool wide_splits(int64_t p, int64_t n, int layout) { return p % kWide == 0 || f2_applies(p, n, layout); }
+
 static size_t gram_ws_one(int64_t p, int64_t n)
 {
     const int64_t nt = cdiv(p, kTile);
     const int64_t tiles = nt * (nt + 1) / 2;
-    const int64_t splits = gram_splits(p, n);
+    const int64_t splits =
+        std::max(gram_splits(p, n, wide_splits(p, n, 0)), gram_splits(p, n, wide_splits(p, n, QE_GRAM_FP32)));
     return kStatusBytes + align256((size_t)splits * tiles * kTileFloats * sizeof(float)) +
            chan_ws_bytes(p, n);
 }
 
 // Token-major X with a token count that is not a multiple of 32 is taken as
-// an aligned part on the 256 x 256 tiles and a short tail (launch_gram).
+// an aligned part on the 256 x 256 tiles and a short tail (launch_gram), where
+// those tiles need aligned token ranges.
 constexpr int64_t kTokAlign = 2 * kX3KC;
 
 size_t gram_ws_bytes(int64_t p, int64_t n)
@@ -614,7 +662,9 @@ qe_status launch_gram(const float* X, int64_t p, int64_t n, int layout, float* S
                       int accumulate, float damp, void* ws, hipStream_t s)
 {
     const bool trans = (layout & ~(QE_GRAM_FP32 | QE_GRAM_BF16X3)) == QE_LAYOUT_NP;
-    if (trans && !(layout & QE_GRAM_FP32) && p % kWide == 0 && n > kTokAlign &&
+    const bool whole = f2_applies(p, n, layout) &&
+                       (gram_splits(p, n, true) != 0 || n <= kSplitTokensMax);
+    if (trans && !(layout & QE_GRAM_FP32) && !whole && p % kWide == 0 && n > kTokAlign &&
         n % kTokAlign != 0) {
         // token rows are contiguous: the tail is X's last n % 32 token rows
         const int64_t tail = n % kTokAlign, main = n - tail;
@@ -631,10 +681,9 @@ static qe_status launch_gram_one(const float* X, int64_t p, int64_t n, int layou
     int* status = static_cast<int*>(ws);
     const int64_t nt = cdiv(p, kTile);
     const int64_t tiles = nt * (nt + 1) / 2;
-    const int64_t splits = gram_splits(p, n);
+    const int64_t splits = gram_splits(p, n, wide_splits(p, n, layout));
     const bool fp32 = (layout & QE_GRAM_FP32) != 0;
-    // the fp16 split (its token-major loader's buffer offsets are 32-bit)
-    const bool f2 = (layout & QE_GRAM_BF16X3) == 0 && p <= (int64_t(1) << 24);
+    const bool f2 = f2_applies(p, n, layout);
     const bool trans = (layout & ~(QE_GRAM_FP32 | QE_GRAM_BF16X3)) == QE_LAYOUT_NP;
     // 16-byte loads need an aligned base and a row stride that keeps them aligned
     const int x_vec4 = aligned16(X) && ((trans ? p : n) % 4 == 0);
@@ -673,17 +722,18 @@ static qe_status launch_gram_one(const float* X, int64_t p, int64_t n, int layou
     hipLaunchKernelGGL((gram_x3_kernel<T, L, F>), dim3(grid), dim3(256), 0, s, X, p, n, nt, tiles, \
                        used, split_len, dst, accumulate, status)
         const bool two = splits == 0;
-        if (full && p % kWide == 0 && (!two || n <= kSplitTokensMax)) {
-            const int64_t ntw = p / kWide;
+        const bool aligned = full && p % kWide == 0;
+        if ((aligned || f2) && (!two || n <= kSplitTokensMax)) {
+            const int64_t ntw = cdiv(p, kWide);
             const int64_t tiles_w = ntw * (ntw + 1) / 2;
             const dim3 grid((unsigned)(8 * cdiv(tiles_w * used, 8)));
             if (f2) {
                 if (trans) {
                     const int64_t sl = chan_slices(p, n);
                     hipLaunchKernelGGL(chan_absmax_np_kernel,
-                                       dim3((unsigned)cdiv(p, 1024), (unsigned)sl), dim3(256), 0, s,
-                                       X, p, n, x_vec4, chpart, status);
-                    hipLaunchKernelGGL(chan_exp_np_kernel, dim3((unsigned)cdiv(p, 256)), dim3(256),
+                                       dim3((unsigned)cdiv(p, 256), (unsigned)sl), dim3(256), 0, s,
+                                       X, p, n, chpart, status);
+                    hipLaunchKernelGGL(chan_exp_np_kernel, dim3((unsigned)cdiv(p, 64)), dim3(256),
                                        0, s, chpart, p, (int)sl, chexp, status);
                 } else {
                     hipLaunchKernelGGL(chan_exp_pn_kernel, dim3((unsigned)p), dim3(256), 0, s, X, n,
@@ -691,20 +741,23 @@ static qe_status launch_gram_one(const float* X, int64_t p, int64_t n, int layou
                 }
                 if (hipGetLastError() != hipSuccess) return QE_ERR_HIP;
             }
-#define QE_GRAM_X3W(D, T, F, SPLITS, LEN, OUT)                                                  \
-    hipLaunchKernelGGL((gram_x3w_kernel<D, T, F>), grid, dim3(512), 0, s, X, p, n, ntw, tiles_w,   \
-                       nt, tiles, SPLITS, LEN, OUT, accumulate, chexp, status)
-            if (f2) {
-                if (two && trans) QE_GRAM_X3W(true, true, true, (int64_t)1, n, Sigma);
-                else if (two) QE_GRAM_X3W(true, false, true, (int64_t)1, n, Sigma);
-                else if (trans) QE_GRAM_X3W(false, true, true, used, split_len, parts);
-                else QE_GRAM_X3W(false, false, true, used, split_len, parts);
-            } else {
-                if (two && trans) QE_GRAM_X3W(true, true, false, (int64_t)1, n, Sigma);
-                else if (two) QE_GRAM_X3W(true, false, false, (int64_t)1, n, Sigma);
-                else if (trans) QE_GRAM_X3W(false, true, false, used, split_len, parts);
-                else QE_GRAM_X3W(false, false, false, used, split_len, parts);
-            }
+#define QE_GRAM_X3W(T, F, E)                                                                    \
+    do {                                                                                        \
+        if (two)                                                                                \
+            hipLaunchKernelGGL((gram_x3w_kernel<true, T, F, E>), grid, dim3(512), 0, s, X, p, n,   \
+                               ntw, tiles_w, nt, tiles, (int64_t)1, n, Sigma, accumulate,       \
+                               chexp, status);                                                  \
+        else                                                                                    \
+            hipLaunchKernelGGL((gram_x3w_kernel<false, T, F, E>), grid, dim3(512), 0, s, X, p, n,  \
+                               ntw, tiles_w, nt, tiles, used, split_len, parts, accumulate,     \
+                               chexp, status);                                                  \
+    } while (0)
+            if (f2 && aligned && trans) QE_GRAM_X3W(true, true, false);
+            else if (f2 && aligned) QE_GRAM_X3W(false, true, false);
+            else if (f2 && trans) QE_GRAM_X3W(true, true, true);
+            else if (f2) QE_GRAM_X3W(false, true, true);
+            else if (trans) QE_GRAM_X3W(true, false, false);
+            else QE_GRAM_X3W(false, false, false);
 #undef QE_GRAM_X3W
         } else if (trans) {
             if (two) { if (full) QE_GRAM_X3(true, true, true); else QE_GRAM_X3(true, true, false); }
@@ -717,8 +770,12 @@ static qe_status launch_gram_one(const float* X, int64_t p, int64_t n, int layou
     }
     if (hipGetLastError() != hipSuccess) return QE_ERR_HIP;
     if (splits != 0) {
-        hipLaunchKernelGGL(gram_finalize_kernel, dim3((unsigned)tiles, kTile / kFinRows), dim3(256),
-                           0, s, parts, tiles, (int)used, nt, Sigma, p, accumulate, status);
+        if (tiles < 128)
+            hipLaunchKernelGGL(gram_finalize_kernel<8>, dim3((unsigned)tiles, kTile / 8), dim3(256), 0, s,
+                               parts, tiles, (int)used, nt, Sigma, p, accumulate, status);
+        else
+            hipLaunchKernelGGL(gram_finalize_kernel<32>, dim3((unsigned)tiles, kTile / 32), dim3(256), 0, s,
+                               parts, tiles, (int)used, nt, Sigma, p, accumulate, status);
         if (hipGetLastError() != hipSuccess) return QE_ERR_HIP;
     }
     if (damp > 0.f) {

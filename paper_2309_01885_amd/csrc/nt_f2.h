@@ -117,20 +117,52 @@ struct F2RowQ {
     }
 };
 
+// The same for any shape: rows from `rows` on repeat the last one (their sums
+// are never stored), tokens from `kvalid` on read as 0, and rows need not be
+// 16-byte aligned (the loads need 4 bytes).  Only a launch's last stages hold
+// tokens past the end; the test is uniform across the workgroup.
+typedef float f32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
+
+struct F2RowQE : F2RowQ {
+    int64_t rows, kvalid;
+    __device__ inline void load_full(int64_t row0, int64_t k0, X3Stage& st) const
+    {
+        const int t = threadIdx.x;
+        const int64_t k = k0 + 4 * (t & 3);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float* src = base + min(row0 + (t >> 2) + 128 * h, rows - 1) * ld + k;
+            if (k0 + kX3KC <= kvalid) {
+                st.v[h] = *reinterpret_cast<const f32x4a4*>(src);
+            } else {
+                st.v[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (k + u < kvalid) st.v[h][u] = src[u];
+            }
+        }
+    }
+};
+
 // Token-major operand with X3Col's staging (thread t: channel t / 2 at eight
 // tokens), read through a buffer descriptor per stage: one 32-bit offset per
 // thread and the token steps as scalar offsets, instead of eight 64-bit
 // addresses.  base = the launch's first token row, ld = p; the descriptor
-// covers the stage's 16 token rows (reads outside it return 0).
+// covers the stage's 16 token rows (EDGE: those of them below kvalid; reads
+// outside it return 0, and a channel from p on reads some value inside it, whose
+// sums are never stored).
+template <bool EDGE>
 struct F2ColB {
     const float* base;
     int64_t ld;
     float sc;
+    int64_t kvalid;
     __device__ inline void load_full(int64_t row0, int64_t k0, X3Stage& st) const
     {
         const int t = threadIdx.x;
+        const int64_t tokens = EDGE ? max((int64_t)0, min((int64_t)16, kvalid - k0)) : 16;
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float*>(base + k0 * ld), 0, (int)(16 * ld * 4), 0x00020000);
+            const_cast<float*>(base + k0 * ld), 0, (int)(tokens * ld * 4), 0x00020000);
         const int vo = (int)((8 * (t & 1) * ld + row0 + (t >> 1)) * 4);
 #pragma unroll
         for (int u = 0; u < 8; ++u)
@@ -255,8 +287,8 @@ __device__ __forceinline__ void f2w_stages(const OA& A, int64_t row0a, const OB&
 }
 
 // acc += A[row0a.., 0..K) B[row0b.., 0..K)^T (scaled values) on the 256 x 256
-// tile of 512 threads; K a positive multiple of 32, every 256-row panel
-// inside the matrix, aligned rows.  `lds` holds NBUF * kF2BufDw dwords.  Ends
+// tile of 512 threads; K a positive multiple of 32 (operands that guard their
+// own edges: tokens from kvalid on read as 0).  `lds` holds NBUF * kF2BufDw dwords.  Ends
 // with a barrier.
 template <int NBUF, class OA, class OB>
 __device__ __forceinline__ void nt_tile_f2_wide(const OA& A, int64_t row0a, const OB& B, int64_t row0b,

@@ -221,3 +221,46 @@ def test_gram_direct_mode_large_p(qe, oracle, layout, n, mode):
     assert np.array_equal(block, blockT.T)
     assert rel_fro(block, ref_block) <= 1e-5
     assert np.max(np.abs(diag - ref_diag) / ref_diag) <= 1e-5
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("p,n", [(129, 181001), (255, 46145), (700, 6127), (1025, 2871), (2300, 569),
+                                 (4097, 179), (256, 33), (512, 1), (768, 15), (257, 15), (385, 31)])
+def test_gram_ragged_wide_tiles(qe, oracle, p, n, layout, offset):
+    """The 256 x 256 tiles past their edges: channels beyond p (one, half a
+    tile, a whole 128 x 128 quarter), tokens beyond n (a stage of 16 partly or
+    wholly empty, a shorter last split), rows and bases that are not 16-byte
+    aligned, with a running sum; the last two shapes have too few products for
+    them and take the guarded 128 x 128 tiles.  The memory around X holds infinities, which
+    any read past its end would carry into Sigma."""
+    spec = synth.CONFIGS["c1"]
+    X = synth.activations(spec, n=n, p=p)
+    Xl = X if layout == 0 else np.ascontiguousarray(X.T)
+    buf = torch.full((Xl.size + offset + 64,), float("inf"), device="cuda")
+    Xd = buf[offset:offset + Xl.size].view(*Xl.shape)
+    Xd.copy_(dev(Xl))
+    S0 = synth.gaussian((p, p), seed=5)
+    S0 = (S0 + S0.T).astype(np.float32)
+    S = host(qe.gram(Xd, layout=layout, Sigma=dev(S0), accumulate=True))
+    # one rounding of each sum onto S0, besides the Gram's own bar
+    assert rel_fro(S, oracle.gram(X) + S0) <= 1e-5
+    assert np.array_equal(S, S.T)
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+def test_gram_direct_mode_ragged(qe, oracle, layout):
+    """33100 channels (no multiple of 128), 45 tokens: the direct mode's last
+    tiles reach past p."""
+    p, n = 33100, 45
+    rng = np.random.default_rng(43)
+    X = rng.standard_t(4, size=(p, n)).astype(np.float32)
+    idx = np.r_[0, 127, 128, np.sort(rng.choice(p - 300, 100, replace=False)) + 130, p - 100:p]
+    idx = np.unique(idx)
+    S = qe.gram(dev(X if layout == 0 else np.ascontiguousarray(X.T)), layout=layout)
+    idx_d = torch.as_tensor(idx, device="cuda")
+    block = host(S[idx_d][:, idx_d])
+    del S
+    torch.cuda.empty_cache()
+    assert np.array_equal(block, block.T)
+    assert rel_fro(block, oracle.gram(X[idx])) <= 1e-5
