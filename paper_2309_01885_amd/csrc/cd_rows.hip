@@ -36,8 +36,6 @@
 
 namespace qe {
 
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-
 struct RowsArgs {
     const float* Sigma;
     const float* inv_d;
@@ -69,7 +67,7 @@ __device__ __forceinline__ int first_sweep(const int* moving, int opt0, int opt1
 template <bool FULL>
 __device__ __forceinline__ f32x4 load4(const float* row, int c, int n)
 {
-    if (FULL || c + 4 <= n) return *reinterpret_cast<const f32x4u*>(row + c);
+    if (FULL || c + 4 <= n) return *reinterpret_cast<const f32x4a4*>(row + c);
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int e = 0; e < 3; ++e)
@@ -239,8 +237,8 @@ __global__ __launch_bounds__(MULTI ? 1024 : 64) void cd_rows_kernel(RowsArgs a)
 #pragma unroll
         for (int e = 0; e < 4; ++e) w[e] = s * ((float)((code[g] >> (8 * e)) & 0xffu) - z);
         if (c + 4 <= n) {
-            *reinterpret_cast<f32x4u*>(Rrow + c) = L[g];
-            *reinterpret_cast<f32x4u*>(Wrow + c) = w;
+            *reinterpret_cast<f32x4a4*>(Rrow + c) = L[g];
+            *reinterpret_cast<f32x4a4*>(Wrow + c) = w;
             if (words) {
                 *reinterpret_cast<uint32_t*>(crow + c) = code[g];
                 continue;

@@ -325,10 +325,10 @@ __global__ __launch_bounds__(512, 1) void gram_x3w_kernel(
         nt_tile_f2_wide<4>(A, ti * kWide, B, tj * kWide, K, lds, acc);
     } else if constexpr (F2 && EDGE) {
         const int r = threadIdx.x >> 2;
-        const F2RowQE A{{X + k0, n, {ldexpf(1.f, cexp(ti * kWide + r)),
-                                     ldexpf(1.f, cexp(ti * kWide + r + 128))}}, p, kv};
-        const F2RowQE B{{X + k0, n, {ldexpf(1.f, cexp(tj * kWide + r)),
-                                     ldexpf(1.f, cexp(tj * kWide + r + 128))}}, p, kv};
+        const F2RowQE A(X + k0, n, ldexpf(1.f, cexp(ti * kWide + r)),
+                        ldexpf(1.f, cexp(ti * kWide + r + 128)), p, ti * kWide, kv);
+        const F2RowQE B(X + k0, n, ldexpf(1.f, cexp(tj * kWide + r)),
+                        ldexpf(1.f, cexp(tj * kWide + r + 128)), p, tj * kWide, kv);
         nt_tile_f2_wide<3>(A, ti * kWide, B, tj * kWide, K, lds, acc);
     } else if constexpr (F2) {
         // this thread stages channels t / 4 and t / 4 + 128 of both panels

@@ -91,144 +91,229 @@ qe_status launch_grid_minmax(const float* W, const float* H, int64_t q, int64_t 
 }
 
 // ---------------------------------------------------------------- exact objective
-// <A, A Sigma> for A = P1 + P2 - P3 (P2, P3 nullable), fused: each 128 x 128
-// tile of A Sigma is formed on matrix cores and immediately dotted with the
-// matching tile of A in fp64; per-tile partials are summed in a fixed order.
-__global__ __launch_bounds__(256, 2) void quad_form_kernel(const float* p1, const float* p2,
-                                                        const float* p3, const float* Sigma,
-                                                        int64_t q, int64_t p, double* partial,
-                                                        int vec4, const int* status)
-{
-    if (failed(status)) return;
-    __shared__ __attribute__((aligned(16))) float lds[kNTLdsFloats];
-    __shared__ double sh[256];
-    const int64_t tn_count = cdiv(p, kTile);
-    const int64_t row0 = (blockIdx.x / tn_count) * kTile, col0 = (blockIdx.x % tn_count) * kTile;
-    f32x16 acc[2][2];
-    zero_acc(acc);
-    // (D Sigma) tile on the bf16 matrix cores with the exact three-way split
-    const X3Comp A{p1, p2, p3, p, q, p};
-    const X3Row B{Sigma, p, p, p};
-    uint32_t* l32 = reinterpret_cast<uint32_t*>(lds);
-    if (vec4 && row0 + kTile <= q && col0 + kTile <= p && p % (2 * kX3KC) == 0)
-        nt_tile_x3_full(A, row0, B, col0, p, l32, acc);
-    else
-        nt_tile_x3_edge(A, row0, B, col0, p, l32, acc);
-    double d = 0.0;
-#pragma unroll
-    for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int64_t r = row0 + acc_row(mi, v), c = col0 + acc_col(ni);
-                if (r < q && c < p) {
-                    const int64_t e = r * p + c;
-                    float a = p2 ? p1[e] + p2[e] : p1[e];
-                    if (p3) a = a - p3[e];
-                    d += (double)a * (double)acc[mi][ni][v];
-                }
-            }
-    const double s = block_sum_f64(d, sh);
-    if (threadIdx.x == 0) partial[blockIdx.x] = s;
-}
-
-// The same on 256 x 256 tiles of eight waves (nt_tile_x3_wide: operand reads
-// pipelined through three LDS stage buffers), for q and p multiples of 256 and
-// aligned rows.  Tiles are dealt to the 8 XCDs in contiguous ranges (the
-// hardware places workgroup b on XCD b % 8) of a banded order (bands of 4 tile
-// rows, column-major inside a band), so that the 32 workgroups an XCD holds
-// at a time share 4 row panels of A and 8 of Sigma in its L2.
-// A = P1 (+ P2) (- P3) with the present terms fixed at compile time, so that
-// the loads in flight hold only the operands that exist.
+// <A, A Sigma> for A = What (+ H) - W and for A = W, on the bf16 matrix cores with
+// the exact three-way split.  Sigma is symmetric, so with column tiles C
+//     <A, A Sigma> = sum_C ( 2 <A_C, sum_{K < C} A_K Sigma_{K,C}> + <A_C, A_C Sigma_{C,C}> ),
+// half the products of the full square.  The sum over K needs no common
+// accumulator: every workgroup forms A_K Sigma_{K,C} for one row tile, one C and
+// a run of at most `chunk` tiles K <= C (twice the tiles before K = C), dots it
+// with its tile of A in fp64 at once, and writes one partial; the partials are
+// summed in a fixed order.  Both forms share one launch.
+//
+// Tiles are 256 x 256 (eight waves, nt_tile_x3_wide) or, where those leave the
+// chip idle, 128 x 128 (four waves); the runs are as long as the number of
+// workgroups allows (see quad_plan).  Rows past the end repeat the last one and
+// are left out of the dot product; rows need no 16-byte alignment.
 template <bool P2, bool P3>
-struct X3CompT {
+struct X3Quad {
     const float *p1, *p2, *p3;
-    int64_t ld;
-    __device__ inline void load_full(int64_t row0, int64_t k0, X3Stage& st) const
+    int64_t off, kvalid;          // this thread's row and half stage, from the bases
+    __device__ inline X3Quad(const float* q1, const float* q2, const float* q3, int64_t ld, int64_t rows,
+                             int64_t row0, int64_t kv)
+        : p1(q1), p2(q2), p3(q3),
+          off(min(row0 + (int)(threadIdx.x >> 1), rows - 1) * ld + 8 * (threadIdx.x & 1)), kvalid(kv)
     {
-        const int t = threadIdx.x;
-        const int64_t off = (row0 + (t >> 1)) * ld + k0 + 8 * (t & 1);
+    }
+    __device__ inline f32x4 at(int64_t e) const
+    {
+        f32x4 v = *reinterpret_cast<const f32x4a4*>(p1 + e);
+        if constexpr (P2) v = v + *reinterpret_cast<const f32x4a4*>(p2 + e);
+        if constexpr (P3) v = v - *reinterpret_cast<const f32x4a4*>(p3 + e);
+        return v;
+    }
+    static __device__ inline float one(const float* p1, const float* p2, const float* p3, int64_t e)
+    {
+        float a = p1[e];
+        if constexpr (P2) a = a + p2[e];
+        if constexpr (P3) a = a - p3[e];
+        return a;
+    }
+    // a stage inside the row's columns (the row is the constructor's)
+    __device__ inline void load_full(int64_t, int64_t k0, X3Stage& st) const
+    {
+        st.v[0] = at(off + k0);
+        st.v[1] = at(off + k0 + 4);
+    }
+    // any stage: columns from kvalid on read as 0
+    __device__ inline void load(int64_t, int64_t k0, X3Stage& st) const
+    {
+        const int64_t k = k0 + 8 * (threadIdx.x & 1);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            f32x4 v = *reinterpret_cast<const f32x4*>(p1 + off + 4 * h);
-            if constexpr (P2) v = v + *reinterpret_cast<const f32x4*>(p2 + off + 4 * h);
-            if constexpr (P3) v = v - *reinterpret_cast<const f32x4*>(p3 + off + 4 * h);
-            st.v[h] = v;
-        }
+        for (int u = 0; u < 8; ++u)
+            st.v[u >> 2][u & 3] = k + u < kvalid ? one(p1, p2, p3, off + k0 + u) : 0.f;
     }
     __device__ inline void store(uint32_t* op, const X3Stage& st) const { x3_store_row8(op, st); }
 };
 
-template <bool P2, bool P3>
-__global__ __launch_bounds__(512, 1) void quad_form_wide_kernel(const float* p1, const float* p2,
-                                                             const float* p3,
-                                                             const float* Sigma, int64_t q,
-                                                             int64_t p, double* partial,
-                                                             const int* status)
+struct QuadArgs {
+    const float *Wh, *H, *W, *Sigma;
+    int64_t q, p, tm, tn;         // row tiles, column tiles
+    int64_t full;                 // runs of `chunk` tiles over all C
+    int64_t units;                // all runs
+    int chunk;
+    double* partial;              // 2 x units x tm
+    const int* status;
+};
+
+// One workgroup's unit of form A: rows row0.., columns 256 or 128 from col0, the
+// tiles K in [k0, col0) twice and, with `diag`, those of K = C once.
+template <int TILE, bool P2, bool P3>
+__device__ __forceinline__ double quad_unit(const QuadArgs& a, const float* p1, const float* p2,
+                                            const float* p3, int64_t row0, int64_t col0, int64_t k0,
+                                            int64_t k1, uint32_t* lds)
 {
-    if (failed(status)) return;
-    __shared__ __attribute__((aligned(16))) uint32_t lds[kX3wLdsDw];
-    __shared__ double sh[512];
-    const int64_t tm_count = q / 256, tn_count = p / 256, tiles = tm_count * tn_count;
-    const int64_t per = cdiv(tiles, 8);
-    const int64_t item = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
-    if (item >= tiles) return;                    // uniform: the whole workgroup leaves
-    const int64_t b0 = (item / (4 * tn_count)) * 4;
-    const int64_t bh = min((int64_t)4, tm_count - b0);
-    const int64_t u = item - b0 * tn_count;
-    const int64_t row0 = (b0 + u % bh) * 256, col0 = (u / bh) * 256;
-    f32x16 acc[2][4];
+    constexpr int NI = TILE == 256 ? 4 : 2;
+    f32x16 acc[2][NI];
 #pragma unroll
     for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < 4; ++ni)
+        for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
-    const X3CompT<P2, P3> A{p1, p2, p3, p};
-    const X3Row B{Sigma, p, p, p};
-    nt_tile_x3_wide(A, row0, B, col0, p, lds, acc);
+#pragma unroll 1
+    for (int part = 0; part < 2; ++part) {
+        const int64_t b = part ? max(k0, col0) : k0, e = part ? k1 : min(k1, col0);
+        if (e > b) {
+            const X3Quad<P2, P3> A(p1 + b, P2 ? p2 + b : nullptr, P3 ? p3 + b : nullptr, a.p, a.q, row0, e - b);
+            const X3Quad<false, false> B(a.Sigma + b, nullptr, nullptr, a.p, a.p, col0, e - b);
+            if constexpr (TILE == 256)
+                nt_tile_x3_wide(A, row0, B, col0, e - b, lds, acc);
+            else if ((e - b) % (2 * kX3KC) == 0)
+                nt_tile_x3_full(A, row0, B, col0, e - b, lds, acc);
+            else
+                nt_tile_x3_edge(A, row0, B, col0, e - b, lds, acc);
+        }
+        if (part == 0) {
+#pragma unroll
+            for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[mi][ni][v] *= 2.f;
+        }
+    }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
     double d = 0.0;
 #pragma unroll
     for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < 4; ++ni)
+        for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int64_t r = row0 + wm * 64 + 32 * mi + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                const int64_t c = col0 + wn * 128 + 32 * ni + (lane & 31);
-                const int64_t e = r * p + c;
-                float a = p1[e];
-                if constexpr (P2) a = a + p2[e];
-                if constexpr (P3) a = a - p3[e];
-                d += (double)a * (double)acc[mi][ni][v];
+                const int64_t r = row0 + (wave >> 1) * 64 + 32 * mi + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+                const int64_t c = col0 + (wave & 1) * (32 * NI) + 32 * ni + (lane & 31);
+                // unconditional loads, all in flight together
+                const float av =
+                    X3Quad<P2, P3>::one(p1, p2, p3, min(r, a.q - 1) * a.p + min(c, a.p - 1));
+                d += (double)av * (double)(r < a.q && c < a.p ? acc[mi][ni][v] : 0.f);
             }
-    sh[threadIdx.x] = d;
-    __syncthreads();
-    for (int st = 256; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) sh[threadIdx.x] += sh[threadIdx.x + st];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partial[item] = sh[0];
+    return d;
 }
 
-__global__ __launch_bounds__(256) void sum_tiles_kernel(const double* partial, int64_t n,
-                                                        double* out, const int* status)
+template <int TILE, bool HASH>
+__global__ __launch_bounds__(2 * TILE, TILE == 256 ? 1 : 2) void quad_kernel(QuadArgs a)
+{
+    if (failed(a.status)) return;
+    __shared__ __attribute__((aligned(16))) uint32_t lds[TILE == 256 ? kX3wLdsDw : kX3LdsDw];
+    __shared__ double sh[TILE / 32];
+    // rows fastest: the workgroups at work at one time share their run of Sigma
+    const int64_t unit = blockIdx.x / (2 * a.tm), slot = blockIdx.x % (2 * a.tm);
+    const bool isw = slot >= a.tm;
+    const int64_t row0 = (slot - (isw ? a.tm : 0)) * TILE;
+    // whole runs first, those of the same K tiles side by side (they share their
+    // tiles of A in L2), then the remainders
+    const int64_t ch = a.chunk;
+    int64_t C, first = 0;
+    if (unit < a.full) {
+        int64_t u = unit, n;
+        for (; u >= (n = a.tn - first - ch + 1); first += ch) u -= n;
+        C = first + ch - 1 + u;
+    } else {
+        int64_t v = unit - a.full, n;
+        for (; v >= (n = min(ch - 1, a.tn - first)); first += ch) v -= n;
+        C = first + n - 1 - v;
+    }
+    const int64_t k0 = first * TILE, k1 = min(a.p, min(first + ch, C + 1) * TILE);
+    double d = isw ? quad_unit<TILE, false, false>(a, a.W, nullptr, nullptr, row0, C * TILE, k0, k1, lds)
+                   : quad_unit<TILE, HASH, true>(a, a.Wh, a.H, a.W, row0, C * TILE, k0, k1, lds);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) d += __shfl_xor(d, o, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = d;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int w = 0; w < TILE / 32; ++w) t += sh[w];
+        a.partial[(isw ? a.units * a.tm : 0) + unit * a.tm + row0 / TILE] = t;
+    }
+}
+
+// Workgroup f: out[f] = the sum of form f's n partials.
+__global__ __launch_bounds__(1024) void quad_sum_kernel(const double* partial, int64_t n, double* out,
+                                                        const int* status)
 {
     if (failed(status)) return;
-    __shared__ double sh[256];
+    __shared__ double sh[16];
+    const double* src = partial + blockIdx.x * n;
     double acc = 0.0;
-    for (int64_t e = threadIdx.x; e < n; e += blockDim.x) acc += partial[e];
-    const double s = block_sum_f64(acc, sh);
-    if (threadIdx.x == 0) *out = s;
+#pragma unroll 4
+    for (int64_t e = threadIdx.x; e < n; e += 1024) acc += src[e];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int w = 0; w < 16; ++w) t += sh[w];
+        out[blockIdx.x] = t;
+    }
+}
+
+struct QuadPlan {
+    int tile, chunk;
+    int64_t tm, tn, full, units;
+};
+
+// Tile and run length.  256 x 256 tiles (one workgroup per CU) need p to be a
+// multiple of 32 and at least 256 units, the others run on 128 x 128 tiles (two
+// per CU).  The run minimises, in tiles of K, the work per slot (or the longest
+// unit) and kQuadUnit for every unit: its pipeline fill and its tile of A, whose
+// 16 us no other workgroup of the CU hides with 256 x 256 tiles (52 us against 37
+// us for a tile of K).  4096 x 4096: 1.21 ms as two launches over the full square,
+// 0.87 ms with runs of 4, 0.75 ms with runs of 16 (the whole C).
+
+static QuadPlan quad_plan(int64_t q, int64_t p)
+{
+    QuadPlan best{};
+    for (int tile : {256, 128}) {
+        if (tile == 256 && p % (2 * kX3KC) != 0) continue;
+        const double slots = tile == 256 ? 256.0 : 512.0;
+        const double kQuadUnit = tile == 256 ? 1.4 : 0.5;
+        double best_cost = 0.0;
+        for (int chunk = 1; chunk <= 32; ++chunk) {
+            QuadPlan pl{tile, chunk, cdiv(q, tile), cdiv(p, tile), 0, 0};
+            for (int64_t C = 0; C < pl.tn; ++C) {
+                pl.full += (C + 1) / chunk;
+                pl.units += cdiv(C + 1, (int64_t)chunk);
+            }
+            const double units = 2.0 * (double)(pl.tm * pl.units);
+            const double work = (double)(pl.tm * pl.tn) * (double)(pl.tn + 1);
+            const double cost = std::max(work / slots, (double)std::min<int64_t>(chunk, pl.tn)) +
+                                kQuadUnit * units / slots;
+            if (chunk == 1 || cost < best_cost) {
+                best = pl;
+                best_cost = cost;
+            }
+            if (chunk == 1 && units < 256.0) break;
+        }
+        if (tile == 256 && 2 * best.tm * best.units >= 256) break;
+    }
+    return best;
 }
 
 size_t objective_ws_bytes(int64_t q, int64_t p)
 {
-    const int64_t tiles = cdiv(q, kTile) * cdiv(p, kTile);
-    return kStatusBytes + 2 * align256(sizeof(double) * tiles);
+    const QuadPlan pl = quad_plan(q, p);
+    return kStatusBytes + align256(sizeof(double) * 2 * pl.tm * pl.units);
 }
 
 qe_status launch_objective(const float* W, const float* Wh, const float* H, const float* Sigma,
@@ -236,37 +321,20 @@ qe_status launch_objective(const float* W, const float* Wh, const float* H, cons
 {
     int* status = static_cast<int*>(ws);
     Ws w(ws);
-    const int64_t tiles = cdiv(q, kTile) * cdiv(p, kTile);
-    double* part0 = w.take<double>(tiles);
-    double* part1 = w.take<double>(tiles);
-    const bool vec4 = aligned16(W) && aligned16(Wh) && aligned16(Sigma) && (!H || aligned16(H)) &&
-                      p % 4 == 0;
-    if (vec4 && q % 256 == 0 && p % 256 == 0) {
-        // 256 x 256 tiles: q p / 65536 partials (fewer than the 128 x 128 count)
-        const int64_t wt = (q / 256) * (p / 256);
-        const dim3 grid((unsigned)(8 * cdiv(wt, 8)));
-        if (H)
-            hipLaunchKernelGGL((quad_form_wide_kernel<true, true>), grid, dim3(512), 0, s, Wh, H,
-                               W, Sigma, q, p, part0, status);
-        else
-            hipLaunchKernelGGL((quad_form_wide_kernel<false, true>), grid, dim3(512), 0, s, Wh,
-                               H, W, Sigma, q, p, part0, status);
-        hipLaunchKernelGGL(sum_tiles_kernel, dim3(1), dim3(256), 0, s, part0, wt, out, status);
-        hipLaunchKernelGGL((quad_form_wide_kernel<false, false>), grid, dim3(512), 0, s, W,
-                           (const float*)nullptr, (const float*)nullptr, Sigma, q, p, part1,
-                           status);
-        hipLaunchKernelGGL(sum_tiles_kernel, dim3(1), dim3(256), 0, s, part1, wt, out + 1, status);
-        return hipGetLastError() == hipSuccess ? QE_OK : QE_ERR_HIP;
-    }
-    // D = What + H - W
-    hipLaunchKernelGGL(quad_form_kernel, dim3((unsigned)tiles), dim3(256), 0, s, Wh, H, W, Sigma,
-                       q, p, part0, vec4 ? 1 : 0, status);
-    hipLaunchKernelGGL(sum_tiles_kernel, dim3(1), dim3(256), 0, s, part0, tiles, out, status);
-    // W itself
-    hipLaunchKernelGGL(quad_form_kernel, dim3((unsigned)tiles), dim3(256), 0, s, W,
-                       (const float*)nullptr, (const float*)nullptr, Sigma, q, p, part1,
-                       vec4 ? 1 : 0, status);
-    hipLaunchKernelGGL(sum_tiles_kernel, dim3(1), dim3(256), 0, s, part1, tiles, out + 1, status);
+    const QuadPlan pl = quad_plan(q, p);
+    const int64_t n = pl.tm * pl.units;
+    double* part = w.take<double>(2 * n);
+    const QuadArgs a{Wh, H, W, Sigma, q, p, pl.tm, pl.tn, pl.full, pl.units, pl.chunk, part, status};
+    const dim3 grid((unsigned)(2 * n)), block((unsigned)(2 * pl.tile));
+    if (pl.tile == 256 && H)
+        hipLaunchKernelGGL((quad_kernel<256, true>), grid, block, 0, s, a);
+    else if (pl.tile == 256)
+        hipLaunchKernelGGL((quad_kernel<256, false>), grid, block, 0, s, a);
+    else if (H)
+        hipLaunchKernelGGL((quad_kernel<128, true>), grid, block, 0, s, a);
+    else
+        hipLaunchKernelGGL((quad_kernel<128, false>), grid, block, 0, s, a);
+    hipLaunchKernelGGL(quad_sum_kernel, dim3(2), dim3(1024), 0, s, part, n, out, status);
     return hipGetLastError() == hipSuccess ? QE_OK : QE_ERR_HIP;
 }
 

@@ -121,24 +121,29 @@ struct F2RowQ {
 // are never stored), tokens from `kvalid` on read as 0, and rows need not be
 // 16-byte aligned (the loads need 4 bytes).  Only a launch's last stages hold
 // tokens past the end; the test is uniform across the workgroup.
-typedef float f32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
-
 struct F2RowQE : F2RowQ {
-    int64_t rows, kvalid;
-    __device__ inline void load_full(int64_t row0, int64_t k0, X3Stage& st) const
+    const float* src[2];          // this thread's rows, at its four tokens of stage 0
+    int64_t kvalid;
+    __device__ inline F2RowQE(const float* x, int64_t stride, float s0, float s1, int64_t rows, int64_t row0,
+                              int64_t kv)
+        : F2RowQ{x, stride, {s0, s1}}, kvalid(kv)
     {
         const int t = threadIdx.x;
-        const int64_t k = k0 + 4 * (t & 3);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            src[h] = x + min(row0 + (t >> 2) + 128 * h, rows - 1) * stride + 4 * (t & 3);
+    }
+    __device__ inline void load_full(int64_t, int64_t k0, X3Stage& st) const
+    {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const float* src = base + min(row0 + (t >> 2) + 128 * h, rows - 1) * ld + k;
             if (k0 + kX3KC <= kvalid) {
-                st.v[h] = *reinterpret_cast<const f32x4a4*>(src);
+                st.v[h] = *reinterpret_cast<const f32x4a4*>(src[h] + k0);
             } else {
                 st.v[h] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    if (k + u < kvalid) st.v[h][u] = src[u];
+                    if (k0 + 4 * (threadIdx.x & 3) + u < kvalid) st.v[h][u] = src[h][k0 + u];
             }
         }
     }

@@ -19,6 +19,7 @@ constexpr int kObjBlocks = 1024;      // workgroups of the fp64 residual dot pro
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4a4 __attribute__((ext_vector_type(4), aligned(4)));   // 16-byte access, 4-byte aligned
 
 __host__ __device__ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 __host__ __device__ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
