@@ -37,3 +37,28 @@ def test_outliers_csr_empty(qe):
     nnz = torch.zeros(1, dtype=torch.int64, device="cuda")
     rowptr, _, _ = qe.outliers_csr(H, sup, nnz)
     assert not np.any(host(rowptr))
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("p", [31, 32, 33, 63, 65, 257])
+def test_pack_codes_group_edges(qe, oracle, bits, p):
+    """Rows that end inside, at and past a group of 32 codes, from a base one byte
+    off; codes past 2^bits keep their low bits."""
+    q = 7
+    codes = synth.integers((q, p), seed=bits + p, lo=0, hi=256).astype(np.uint8)
+    buf = torch.full((q * p + 33,), 255, dtype=torch.uint8, device="cuda")
+    cd = buf[1:1 + q * p].view(q, p)
+    cd.copy_(dev(codes))
+    want = oracle.pack_codes(codes & np.uint8(2 ** bits - 1), bits)
+    assert np.array_equal(host(qe.pack_codes(cd, bits)), want)
+
+
+@pytest.mark.parametrize("q,p,n", [(1, 40, 17), (16, 33, 40), (4100, 64, 900), (300, 257, 1), (50, 20, 1000)])
+def test_outliers_csr_row_search(qe, q, p, n):
+    """Empty rows at both ends and in runs, one entry, every entry."""
+    lin = np.sort(np.random.default_rng(q).choice(q * p, size=n, replace=False)).astype(np.int64)
+    H = synth.gaussian((q, p), seed=q)
+    rowptr, cols, vals = qe.outliers_csr(dev(H), dev(lin), dev(np.array([n], np.int64)))
+    assert np.array_equal(host(rowptr), np.searchsorted(lin, np.arange(q + 1) * p))
+    assert np.array_equal(host(cols), lin % p)
+    assert np.array_equal(host(vals), H.reshape(-1)[lin])
