@@ -31,6 +31,7 @@
 // barriers, more reuse of Sigma rows in L2) took 10 to 30% longer, and 8 waves
 // of 1536 columns at p = 11008 (139 registers) 25% longer than 11 of 1024.
 #include <algorithm>
+#include <utility>
 
 #include "qe_internal.h"
 
@@ -88,60 +89,66 @@ __device__ __forceinline__ void apply_move(f32x4 (&L)[G], const float* srow, int
         for (int e = 0; e < 4; ++e) L[g][e] = fmaf(delta, v[g][e], L[g][e]);
 }
 
-// One turn: the wave's columns in order.  Returns the number of moves.
-template <int G, bool FULL>
-__device__ __forceinline__ int take_turn(const RowsArgs& a, f32x4 (&L)[G], uint32_t (&code)[G], int c0,
-                                         int wcol, float s, float inv_s, int2* list, double& f)
+// One group of 256 columns of the wave's turn.  Returns the number of moves so far.
+template <int G, int g, bool FULL>
+__device__ __forceinline__ int take_group(const RowsArgs& a, f32x4 (&L)[G], uint32_t (&code)[G], int c0,
+                                          int wcol, float s, float inv_s, int2* list, double& f, int cnt)
 {
     const int lane = threadIdx.x & 63;
     const int n = (int)a.p;
-    int cnt = 0;
+    if (!FULL && wcol + 256 * g >= n) return cnt;
+    f32x4 u = load4<FULL>(a.inv_d, c0 + 256 * g, n);
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        if (!FULL && wcol + 256 * g >= n) break;
-        f32x4 u = load4<FULL>(a.inv_d, c0 + 256 * g, n);
+    for (int e = 0; e < 4; ++e) u[e] *= inv_s;
+    // the columns still to be taken: inside the row, behind the last move
+    uint64_t open[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) u[e] *= inv_s;
-        // the columns still to be taken: inside the row, behind the last move
-        uint64_t open[4];
+    for (int e = 0; e < 4; ++e) open[e] = FULL ? ~0ull : __ballot(c0 + 256 * g + e < n);
+    for (;;) {
+        float d[4];
+        uint64_t m[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) open[e] = FULL ? ~0ull : __ballot(c0 + 256 * g + e < n);
-        for (;;) {
-            float d[4];
-            uint64_t m[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float kc = (float)((code[g] >> (8 * e)) & 0xffu);
-                // Lemma 1's minimiser on the grid axis, its nearest level; a valid,
-                // equally near current level is kept (Sec. 3.3)
-                const float t = fmaf(-L[g][e], u[e], kc);
-                const float kn = __builtin_amdgcn_fmed3f(rintf(t), 0.f, a.maxq);
-                d[e] = kn - kc;
-                m[e] = __ballot(d[e] != 0.f && !(fabsf(t - kc) <= fabsf(t - kn))) & open[e];
-            }
-            const uint64_t any = m[0] | m[1] | m[2] | m[3];
-            if (any == 0) break;
-            const int ls = __builtin_ctzll(any);
-            const int es = (m[0] >> ls) & 1 ? 0 : (m[1] >> ls) & 1 ? 1 : (m[2] >> ls) & 1 ? 2 : 3;
-            const float dsel = es == 0 ? d[0] : es == 1 ? d[1] : es == 2 ? d[2] : d[3];
-            const float dm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(dsel), ls));
-            const float delta = s * dm;
-            const int j = wcol + 256 * g + 4 * ls + es;
-            const uint64_t behind = (~0ull << ls) << 1;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) open[e] &= behind | (e > es ? 1ull << ls : 0ull);
-            if (list && lane == 0) list[cnt] = make_int2(j, __float_as_int(delta));
-            const float r0 = es == 0 ? L[g][0] : es == 1 ? L[g][1] : es == 2 ? L[g][2] : L[g][3];
-            apply_move<G, FULL>(L, a.Sigma + (int64_t)j * a.p, c0, n, delta);
-            const float r1 = es == 0 ? L[g][0] : es == 1 ? L[g][1] : es == 2 ? L[g][2] : L[g][3];
-            if (lane == ls) {
-                code[g] += (uint32_t)((int)dm << (8 * es));
-                // the move changes f by delta (2 R + delta Sigma_jj) = delta (R + R')
-                f += (double)delta * ((double)r0 + (double)r1);
-            }
-            ++cnt;
+        for (int e = 0; e < 4; ++e) {
+            const float kc = (float)((code[g] >> (8 * e)) & 0xffu);
+            // Lemma 1's minimiser on the grid axis, its nearest level; a valid,
+            // equally near current level is kept (Sec. 3.3)
+            const float t = fmaf(-L[g][e], u[e], kc);
+            const float kn = __builtin_amdgcn_fmed3f(rintf(t), 0.f, a.maxq);
+            d[e] = kn - kc;
+            m[e] = __ballot(d[e] != 0.f && !(fabsf(t - kc) <= fabsf(t - kn))) & open[e];
         }
+        const uint64_t any = m[0] | m[1] | m[2] | m[3];
+        if (any == 0) return cnt;
+        const int ls = __builtin_ctzll(any);
+        const int es = (m[0] >> ls) & 1 ? 0 : (m[1] >> ls) & 1 ? 1 : (m[2] >> ls) & 1 ? 2 : 3;
+        const float dsel = es == 0 ? d[0] : es == 1 ? d[1] : es == 2 ? d[2] : d[3];
+        const float dm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(dsel), ls));
+        const float delta = s * dm;
+        const int j = wcol + 256 * g + 4 * ls + es;
+        const uint64_t behind = (~0ull << ls) << 1;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) open[e] &= behind | (e > es ? 1ull << ls : 0ull);
+        if (list && lane == 0) list[cnt] = make_int2(j, __float_as_int(delta));
+        const float r0 = es == 0 ? L[g][0] : es == 1 ? L[g][1] : es == 2 ? L[g][2] : L[g][3];
+        apply_move<G, FULL>(L, a.Sigma + (int64_t)j * a.p, c0, n, delta);
+        const float r1 = es == 0 ? L[g][0] : es == 1 ? L[g][1] : es == 2 ? L[g][2] : L[g][3];
+        if (lane == ls) {
+            code[g] += (uint32_t)((int)dm << (8 * es));
+            // the move changes f by delta (2 R + delta Sigma_jj) = delta (R + R')
+            f += (double)delta * ((double)r0 + (double)r1);
+        }
+        ++cnt;
     }
+}
+
+// One turn: the wave's columns in order.  Returns the number of moves.
+template <int G, bool FULL, int... g>
+__device__ __forceinline__ int take_turn(std::integer_sequence<int, g...>, const RowsArgs& a, f32x4 (&L)[G],
+                                         uint32_t (&code)[G], int c0, int wcol, float s, float inv_s,
+                                         int2* list, double& f)
+{
+    int cnt = 0;
+    ((cnt = take_group<G, g, FULL>(a, L, code, c0, wcol, s, inv_s, list, f, cnt)), ...);
     return cnt;
 }
 
@@ -182,6 +189,7 @@ __global__ __launch_bounds__(MULTI ? 1024 : 64) void cd_rows_kernel(RowsArgs a)
                 code[g] |= (uint32_t)__builtin_amdgcn_fmed3f(rintf(fmaf(w[e], inv_s, z)), 0.f, 255.f)
                            << (8 * e);
     }
+    constexpr auto groups = std::make_integer_sequence<int, G>{};
     int turn = 0;
     for (int sw = start; sw < a.k1; ++sw) {
         double f = 0.0;
@@ -189,8 +197,8 @@ __global__ __launch_bounds__(MULTI ? 1024 : 64) void cd_rows_kernel(RowsArgs a)
         for (int w = 0; w < W; ++w, turn ^= 1) {
             int2* li = MULTI ? list[turn] : nullptr;
             if (wave == w) {
-                const int cnt = full ? take_turn<G, true>(a, L, code, c0, wcol, s, inv_s, li, f)
-                                     : take_turn<G, false>(a, L, code, c0, wcol, s, inv_s, li, f);
+                const int cnt = full ? take_turn<G, true>(groups, a, L, code, c0, wcol, s, inv_s, li, f)
+                                     : take_turn<G, false>(groups, a, L, code, c0, wcol, s, inv_s, li, f);
                 if (lane == 0) count[turn] = cnt;
             }
             __syncthreads();

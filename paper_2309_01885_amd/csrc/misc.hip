@@ -341,31 +341,52 @@ qe_status launch_objective(const float* W, const float* Wh, const float* H, cons
 // ---------------------------------------------------------------- lambda_max
 // Power method (Sec. 4.3): v_k = y_{k-1} / ||y_{k-1}|| (v_0 = 1/sqrt(p)),
 // y_k = Sigma v_k, lambda_k = v_k . y_k (Rayleigh quotient of the unit v_k).
-// One kernel per iteration: every workgroup first forms 1/||y_{k-1}|| from the
+// One kernel per iteration: every workgroup forms 8 rows of Sigma y_{k-1} (two per
+// wavefront, processed together so that each float4 of y_{k-1} serves two rows of
+// Sigma; fp64 dot products against y_{k-1} itself), then 1/||y_{k-1}|| from the
 // previous iteration's per-workgroup partials (same fixed-order sum in every
-// workgroup), then 8 rows of y_k (two per wavefront, processed together so
-// that each float4 of y_{k-1} serves two rows of Sigma; fp64 dot products
-// against y_{k-1} itself, the normalisation applied once per row), and writes
-// its partials of ||y_k||^2 and v_k . y_k.  Workgroup 0 also records
+// workgroup), applies it once per row, and writes its partials of ||y_k||^2 and
+// v_k . y_k.  Workgroup 0 also records
 // lambda_{k-1}.  Sigma is read once per iteration: the kernel is bound by
 // that stream (HBM or, for Sigma within the die-level cache, that cache).
 constexpr int kSymvRows = 8;
 constexpr int kLambdaCheck = 32;   // iterations per host check (the stop is still per iteration)
 
-// Sums the per-workgroup partials (|Sv|^2, v'Sv, |v|^2) of one iteration.
-__device__ inline void sum_partials3(const double* part, int n, double* sh, double& yy,
-                                     double& vy, double& vv)
-{
-    double a = 0.0, b = 0.0, c = 0.0;
-    for (int e = threadIdx.x; e < n; e += blockDim.x) {
-        a += part[3 * e];
-        b += part[3 * e + 1];
-        c += part[3 * e + 2];
+// The per-workgroup partials (|Sv|^2, v'Sv, |v|^2) of one iteration: early() fetches
+// this thread's first kEarly of each, before the iteration's own loads are waited
+// for, and sum() adds all of them in a fixed order (every thread gets the sums).
+struct Partials3 {
+    static constexpr int kEarly = 2;
+    double v[kEarly][3];
+    __device__ inline void early(const double* part, int n)
+    {
+#pragma unroll
+        for (int k = 0; k < kEarly; ++k) {
+            const int e = threadIdx.x + 256 * k;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[k][c] = e < n ? part[3 * e + c] : 0.0;
+        }
     }
-    yy = block_sum_f64(a, sh);
-    vy = block_sum_f64(b, sh);
-    vv = block_sum_f64(c, sh);
-}
+    __device__ inline void sum(const double* part, int n, double (&sh)[4][3], double (&out)[3]) const
+    {
+        double a[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) a[c] = v[0][c] + v[1][c];
+        for (int e = threadIdx.x + 256 * kEarly; e < n; e += 256)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) a[c] += part[3 * e + c];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) a[c] += __shfl_xor(a[c], o, 64);
+        if ((threadIdx.x & 63) == 0)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) sh[threadIdx.x >> 6][c] = a[c];
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < 3; ++c) out[c] = ((sh[0][c] + sh[1][c]) + sh[2][c]) + sh[3][c];
+    }
+};
 
 // Quotient rho = v'Sv / v'v and squared inclusion radius |Sv - rho v|^2 / |v|^2
 // (= (|Sv|^2 - (v'Sv)^2 / v'v) / v'v) of one iteration, into lam_hist.
@@ -384,19 +405,11 @@ __global__ __launch_bounds__(256) void power_step_kernel(const float* __restrict
                                                          int first, int vec4, float* y,
                                                          double* part, double* lam_hist, int slot)
 {
-    __shared__ double sh[256];
+    __shared__ double sh[4][3];
     __shared__ double wpart[4][3];
     const int nwg = (int)gridDim.x;
-    // v_k = yprev * inv (the first iteration: yprev taken as all ones)
-    double inv;
-    if (first) {
-        inv = 1.0 / sqrt((double)p);
-    } else {
-        double yy, vy, vv;
-        sum_partials3(pprev, nwg, sh, yy, vy, vv);
-        inv = yy > 0.0 ? 1.0 / sqrt(yy) : 0.0;
-        if (blockIdx.x == 0 && threadIdx.x == 0 && slot > 0) put_hist(lam_hist, slot - 1, yy, vy, vv);
-    }
+    Partials3 prev;
+    prev.early(pprev, first ? 0 : nwg);
     auto wj = [&](int64_t j) -> float { return first ? 1.f : yprev[j]; };
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     constexpr int RW = kSymvRows / 4;            // rows per wavefront
@@ -432,6 +445,17 @@ __global__ __launch_bounds__(256) void power_step_kernel(const float* __restrict
 #pragma unroll
         for (int rr = 0; rr < RW; ++rr) acc[rr] += (double)srow[rr][j] * wv;
     }
+    // v_k = yprev * inv (the first iteration: yprev taken as all ones).  Only now,
+    // behind the stream of Sigma: it is not needed before.
+    double inv;
+    if (first) {
+        inv = 1.0 / sqrt((double)p);
+    } else {
+        double t[3];
+        prev.sum(pprev, nwg, sh, t);
+        inv = t[0] > 0.0 ? 1.0 / sqrt(t[0]) : 0.0;
+        if (blockIdx.x == 0 && threadIdx.x == 0 && slot > 0) put_hist(lam_hist, slot - 1, t[0], t[1], t[2]);
+    }
     double pyy = 0.0, pvy = 0.0, pvv = 0.0;
 #pragma unroll
     for (int rr = 0; rr < RW; ++rr) {
@@ -462,10 +486,12 @@ __global__ __launch_bounds__(256) void power_step_kernel(const float* __restrict
 __global__ __launch_bounds__(256) void power_last_kernel(const double* part, int nwg,
                                                          double* lam_hist, int slot)
 {
-    __shared__ double sh[256];
-    double yy, vy, vv;
-    sum_partials3(part, nwg, sh, yy, vy, vv);
-    if (threadIdx.x == 0) put_hist(lam_hist, slot, yy, vy, vv);
+    __shared__ double sh[4][3];
+    Partials3 last;
+    last.early(part, nwg);
+    double t[3];
+    last.sum(part, nwg, sh, t);
+    if (threadIdx.x == 0) put_hist(lam_hist, slot, t[0], t[1], t[2]);
 }
 
 size_t lambda_ws_bytes(int64_t p)
