@@ -193,8 +193,7 @@ struct StepArgs {
     int dense;            // no sparse block update (every tile on the matrix cores)
     int n_panel;          // workgroups [0, n_panel) run the panel
     int64_t tiles_n;      // GEMM column tiles
-    int sig_vec4;
-    int r_vec4;           // R allows aligned 16-byte row access
+    int sig_vec4;         // Sigma allows aligned 16-byte row access (fp32 products)
     int* nzcur;           // q: nonzero code differences of each row in the current super-block
     const int* nzprev;    // q: the same for the previous super-block (code differences only)
     double* fpart;        // per panel wave: the objective change of this sweep's moves so far
@@ -332,78 +331,52 @@ __device__ __forceinline__ void panel_run(std::integer_sequence<int, Js...>,
     (panel_step<SLOTS, Js, FULL, RELAX, INTD>(st, sS, g, width, s, z, maxq), ...);
 }
 
-// Stages Sigma[r0 + k][c0 + c] (k < kw, c < cw; else 0) into LDS with the
-// column permutation used by the panel: column c = 16 m + g sits at g * SLOTS + m.
-// Full blocks issue all their loads before the first LDS store, so the global
-// latency is paid once per block.
+// Stages Sigma[r0 + k][c0 + c] (k < kw, c < cw) into LDS with the column
+// permutation used by the panel: column c = 16 m + g sits at g * SLOTS + m.  Rows
+// and columns past the end repeat the last one (no column step takes them).
+// Thread t takes (row k, lane g) pairs: the lane's SLOTS columns g, g + 16, ... of
+// row k, read as single floats (16 lanes of a wave cover 64 contiguous bytes of a
+// row), written as float4 runs of the panel layout (a quarter of the LDS store
+// instructions of element-wise stores).  All loads are issued before the first
+// LDS store, so the global latency is paid once per block.
 template <int SLOTS>
 __device__ __forceinline__ void stage_sigma_block(const float* __restrict__ Sigma, int64_t p,
-                                                  int64_t r0, int kw, int64_t c0, int cw,
-                                                  bool vec4, float* sS)
+                                                  int64_t r0, int kw, int64_t c0, int cw, float* sS)
 {
     constexpr int B = 16 * SLOTS;
-    constexpr int Q = B / 4;                     // float4 per row
-    constexpr int PER = (B * Q + 255) / 256;     // float4 per thread
-    if constexpr (SLOTS % 4 == 0) {
-        if (kw == B && cw == B) {
-            // thread t takes (row k, lane g) pairs: the lane's SLOTS columns
-            // g, g + 16, ... of row k, read as single floats (16 lanes of a
-            // wave cover 64 contiguous bytes of a row), written as float4
-            // runs of the panel layout (a quarter of the LDS store
-            // instructions of element-wise stores)
-            constexpr int PPT = B * 16 / 256;    // pairs per thread
-            float v[PPT][SLOTS];
+    constexpr int PPT = B * 16 / 256;    // pairs per thread
+    float v[PPT][SLOTS];
 #pragma unroll
-            for (int u = 0; u < PPT; ++u) {
-                const int pi = threadIdx.x + 256 * u;
-                const int k = pi >> 4, g = pi & 15;
-                const float* src = Sigma + (r0 + k) * p + c0 + g;
+    for (int u = 0; u < PPT; ++u) {
+        const int pi = threadIdx.x + 256 * u;
+        const int k = min(pi >> 4, kw - 1), g = pi & 15;
+        const float* src = Sigma + (r0 + k) * p + c0;
+        if (cw == B) {
 #pragma unroll
-                for (int m = 0; m < SLOTS; ++m) v[u][m] = src[16 * m];
-            }
+            for (int m = 0; m < SLOTS; ++m) v[u][m] = src[g + 16 * m];
+        } else {
 #pragma unroll
-            for (int u = 0; u < PPT; ++u) {
-                const int pi = threadIdx.x + 256 * u;
-                const int k = pi >> 4, g = pi & 15;
-#pragma unroll
-                for (int m4 = 0; m4 < SLOTS / 4; ++m4)
-                    *reinterpret_cast<f32x4*>(sS + k * B + g * SLOTS + 4 * m4) =
-                        f32x4{v[u][4 * m4], v[u][4 * m4 + 1], v[u][4 * m4 + 2], v[u][4 * m4 + 3]};
-            }
-            return;
+            for (int m = 0; m < SLOTS; ++m) v[u][m] = src[min(g + 16 * m, cw - 1)];
         }
     }
-    if (vec4 && kw == B && cw == B) {
-        f32x4 v[PER];
 #pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int f = threadIdx.x + 256 * u;
-            if (f < B * Q)
-                v[u] = *reinterpret_cast<const f32x4*>(Sigma + (r0 + f / Q) * p + c0 + 4 * (f % Q));
+    for (int u = 0; u < PPT; ++u) {
+        const int pi = threadIdx.x + 256 * u;
+        float* dst = sS + (pi >> 4) * B + (pi & 15) * SLOTS;
+        if constexpr (SLOTS % 4 == 0) {
+#pragma unroll
+            for (int m4 = 0; m4 < SLOTS / 4; ++m4)
+                *reinterpret_cast<f32x4*>(dst + 4 * m4) =
+                    f32x4{v[u][4 * m4], v[u][4 * m4 + 1], v[u][4 * m4 + 2], v[u][4 * m4 + 3]};
+        } else {
+#pragma unroll
+            for (int m = 0; m < SLOTS; ++m) dst[m] = v[u][m];
         }
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int f = threadIdx.x + 256 * u;
-            if (f >= B * Q) continue;
-            const int k = f / Q, cb = 4 * (f % Q);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int cc = cb + e;
-                sS[k * B + (cc & 15) * SLOTS + (cc >> 4)] = v[u][e];
-            }
-        }
-        return;
-    }
-    for (int e = threadIdx.x; e < B * B; e += blockDim.x) {
-        const int k = e / B, cc = e % B;
-        float x = 0.f;
-        if (k < kw && cc < cw) x = Sigma[(r0 + k) * p + c0 + cc];
-        sS[k * B + (cc & 15) * SLOTS + (cc >> 4)] = x;
     }
 }
 
 // L_{i,J} += dscale_i D_{i, k0..k0+kw} Sigma_{r0..r0+kw, J} for the workgroup's
-// 16 rows (kw <= B), with D a q x S row-major delta buffer and dscale the row's
+// 16 rows (kw = B: an earlier block of the super-block is whole), with D a q x S row-major delta buffer and dscale the row's
 // grid step when D holds code differences (else 1).
 //
 // B >= 64: on matrix cores (v_mfma_f32_16x16x4f32, 16 x 16 output tiles; wave
@@ -435,46 +408,29 @@ __device__ __forceinline__ void add_block_update(PanelState<SLOTS>& st, const St
         // Sigma staged transposed: sT[c][k] = Sigma[j0 + c][r0 + k]
         constexpr int PER = B * (B / 4) / 256;  // float4 per thread
         constexpr int HALF = PER >= 8 ? PER / 2 : PER;   // in flight at once (register budget)
-        if (kw == B && width == B && a.sig_vec4) {
 #pragma unroll
-            for (int u0 = 0; u0 < PER; u0 += HALF) {
-                f32x4 v[HALF];
+        for (int u0 = 0; u0 < PER; u0 += HALF) {
+            f32x4 v[HALF];
 #pragma unroll
-                for (int u = 0; u < HALF; ++u) {
-                    const int f = threadIdx.x + 256 * (u0 + u);
-                    v[u] = *reinterpret_cast<const f32x4*>(a.Sigma + (j0 + f / (B / 4)) * a.p +
-                                                           r0 + 4 * (f % (B / 4)));
-                }
-#pragma unroll
-                for (int u = 0; u < HALF; ++u) {
-                    const int f = threadIdx.x + 256 * (u0 + u);
-                    *reinterpret_cast<f32x4*>(sT + (f / (B / 4)) * kTStride + 4 * (f % (B / 4))) =
-                        v[u];
-                }
+            for (int u = 0; u < HALF; ++u) {
+                const int f = threadIdx.x + 256 * (u0 + u);
+                // (columns past the block's width repeat the last one)
+                v[u] = *reinterpret_cast<const f32x4a4*>(
+                    a.Sigma + (j0 + min(f / (B / 4), width - 1)) * a.p + r0 + 4 * (f % (B / 4)));
             }
-        } else {
-            for (int e = threadIdx.x; e < B * B; e += blockDim.x) {
-                const int cc = e / B, k = e % B;
-                sT[cc * kTStride + k] =
-                    (cc < width && k < kw) ? a.Sigma[(j0 + cc) * a.p + r0 + k] : 0.f;
+#pragma unroll
+            for (int u = 0; u < HALF; ++u) {
+                const int f = threadIdx.x + 256 * (u0 + u);
+                *reinterpret_cast<f32x4*>(sT + (f / (B / 4)) * kTStride + 4 * (f % (B / 4))) = v[u];
             }
         }
         // A fragments: row i0 + r, k = 16 kg + 4h .. +3 (fetched after the Sigma
         // loads retire, to keep both sets from being live at once)
         f32x4 av[KG];
-        const int64_t ia = i0 + r;
-        const bool full = kw == B && i0 + 16 <= a.q;
+        const int64_t ia = min(i0 + r, a.q - 1);
 #pragma unroll
-        for (int kg = 0; kg < KG; ++kg) {
-            const int kk = 16 * kg + 4 * h;
-            if (full) {
-                av[kg] = *reinterpret_cast<const f32x4*>(D + ia * a.S + k0 + kk);
-            } else {
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    av[kg][u] = (ia < a.q && kk + u < kw) ? D[ia * a.S + k0 + kk + u] : 0.f;
-            }
-        }
+        for (int kg = 0; kg < KG; ++kg)
+            av[kg] = *reinterpret_cast<const f32x4*>(D + ia * a.S + k0 + 16 * kg + 4 * h);
         __syncthreads();
         f32x4 acc[T];
 #pragma unroll
@@ -504,7 +460,7 @@ __device__ __forceinline__ void add_block_update(PanelState<SLOTS>& st, const St
         float* sS = lds;            // B x B
         float* sD = lds + B * B;    // 16 x B
         __syncthreads();            // staging buffers free
-        stage_sigma_block<SLOTS>(a.Sigma, a.p, r0, kw, j0, width, a.sig_vec4 != 0, sS);
+        stage_sigma_block<SLOTS>(a.Sigma, a.p, r0, kw, j0, width, sS);
         for (int e = threadIdx.x; e < 16 * B; e += blockDim.x) {
             const int rr = e / B, k = e % B;
             const int64_t ii = i0 + rr;
@@ -536,7 +492,8 @@ constexpr int kLaStride = kLaK + 4;       // LDS row stride (floats) of a staged
 constexpr int kLaCols = 256;              // super-block columns covered
 constexpr int kLaUStride = kLaCols + 4;   // LDS row stride of the 16 x 256 result
 
-template <bool FULL>
+// Rows and columns past the end repeat the last one (their results are not
+// stored); the previous super-block is always whole.
 __device__ __forceinline__ void la_fetch(const StepArgs& a, int64_t i0, int kc, f32x4 (&v)[16],
                                          f32x4 (&av)[4])
 {
@@ -545,38 +502,25 @@ __device__ __forceinline__ void la_fetch(const StepArgs& a, int64_t i0, int kc, 
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
         const int f = threadIdx.x + 256 * u;
-        const int c = f >> 4, kq = f & 15;
-        const int64_t base = (a.sb + c) * a.p + a.psb + kc + 4 * kq;
-        if constexpr (FULL) {
-            v[u] = *reinterpret_cast<const f32x4*>(a.Sigma + base);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                v[u][e] = (c < a.sbw && kc + 4 * kq + e < a.psbw) ? a.Sigma[base + e] : 0.f;
-        }
+        const int c = min(f >> 4, a.sbw - 1), kq = f & 15;
+        v[u] = *reinterpret_cast<const f32x4a4*>(a.Sigma + (a.sb + c) * a.p + a.psb + kc + 4 * kq);
     }
-    const int64_t ia = i0 + r;
+    const int64_t ia = min(i0 + r, a.q - 1);
 #pragma unroll
-    for (int kg = 0; kg < 4; ++kg) {
-        const int k = kc + 16 * kg + 4 * h;
-        if constexpr (FULL) {
-            av[kg] = *reinterpret_cast<const f32x4*>(a.dprev + ia * a.S + k);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                av[kg][e] = (ia < a.q && k + e < a.psbw) ? a.dprev[ia * a.S + k + e] : 0.f;
-        }
-    }
+    for (int kg = 0; kg < 4; ++kg)
+        av[kg] = *reinterpret_cast<const f32x4*>(a.dprev + ia * a.S + kc + 16 * kg + 4 * h);
 }
 
-template <bool FULL>
-__device__ __forceinline__ void lookahead_k(const StepArgs& a, float* lds, int64_t i0,
-                                            f32x4 (&acc)[4])
+__device__ __forceinline__ void lookahead(const StepArgs& a, float* lds, int64_t i0, int lrow,
+                                          int g, bool rowok, float dscale)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 15, h = lane >> 4;
+    f32x4 acc[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 v[16], av[4], avn[4];
-    la_fetch<FULL>(a, i0, 0, v, avn);
+    la_fetch(a, i0, 0, v, avn);
     for (int kc = 0; kc < a.psbw; kc += kLaK) {
         __syncthreads();                         // the previous chunk's reads are done
 #pragma unroll
@@ -587,7 +531,7 @@ __device__ __forceinline__ void lookahead_k(const StepArgs& a, float* lds, int64
 #pragma unroll
         for (int kg = 0; kg < 4; ++kg) av[kg] = avn[kg];
         __syncthreads();
-        if (kc + kLaK < a.psbw) la_fetch<FULL>(a, i0, kc + kLaK, v, avn);   // in flight below
+        if (kc + kLaK < a.psbw) la_fetch(a, i0, kc + kLaK, v, avn);   // in flight below
 #pragma unroll
         for (int kg = 0; kg < 4; ++kg)
 #pragma unroll
@@ -599,20 +543,6 @@ __device__ __forceinline__ void lookahead_k(const StepArgs& a, float* lds, int64
                     acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[kg][u], bv[u], acc[t], 0, 0, 0);
             }
     }
-}
-
-__device__ __forceinline__ void lookahead(const StepArgs& a, float* lds, int64_t i0, int lrow,
-                                          int g, bool rowok, float dscale)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int r = lane & 15, h = lane >> 4;
-    f32x4 acc[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (a.sig_vec4 && a.sbw == kLaCols && a.psbw % kLaK == 0 && i0 + 16 <= a.q)
-        lookahead_k<true>(a, lds, i0, acc);
-    else
-        lookahead_k<false>(a, lds, i0, acc);
     __syncthreads();                             // the last chunk's reads are done
     float* sU = lds;                             // 16 x 256 result
     // 16 x 16 output: lane holds rows 4 (lane / 16) + v, column lane % 16
@@ -776,7 +706,7 @@ __device__ __forceinline__ void panel_role(const StepArgs& a, float* lds)
                                     width, i0, lrow, g, lds, dscale);
         // (3) the B column updates in order
         __syncthreads();
-        stage_sigma_block<SLOTS>(a.Sigma, p, j0, width, j0, width, a.sig_vec4 != 0, sS);
+        stage_sigma_block<SLOTS>(a.Sigma, p, j0, width, j0, width, sS);
         __syncthreads();
         constexpr auto cols = std::make_integer_sequence<int, B>{};
         if (a.relax)
@@ -887,7 +817,7 @@ __device__ __forceinline__ void gemm_sparse(const StepArgs& a, int* li, int nz, 
     const int64_t c0 = col0 + 2 * lane;
     const bool ok0 = c0 < a.p && !(c0 >= ex0 && c0 < ex1);
     const bool ok1 = c0 + 1 < a.p && !(c0 + 1 >= ex0 && c0 + 1 < ex1);
-    const bool pair = a.sig_vec4 && a.r_vec4 && c0 + 1 < a.p;   // 8-byte aligned pairs
+    const bool pair = c0 + 1 < a.p;
     for (int j0 = wave; j0 < active; j0 += 4 * kSpPass) {
         int64_t ir[kSpPass];
         int cn[kSpPass];
@@ -909,7 +839,7 @@ __device__ __forceinline__ void gemm_sparse(const StepArgs& a, int* li, int nz, 
             }
             const float* rrow = a.R + ir[u] * a.p;
             if (pair) {
-                const f32x2 v = *reinterpret_cast<const f32x2*>(rrow + c0);
+                const f32x2 v = *reinterpret_cast<const f32x2a4*>(rrow + c0);
                 r0v[u] = v[0];
                 r1v[u] = v[1];
             } else {
@@ -951,7 +881,7 @@ __device__ __forceinline__ void gemm_sparse(const StepArgs& a, int* li, int nz, 
                     dn[u][n] = __int_as_float(en.y);
                     const float* srow = a.Sigma + (a.psb + en.x) * a.p;
                     if (pair) {
-                        const f32x2 sv = *reinterpret_cast<const f32x2*>(srow + c0);
+                        const f32x2 sv = *reinterpret_cast<const f32x2a4*>(srow + c0);
                         s0[u][n] = sv[0];
                         s1[u][n] = sv[1];
                     } else {
@@ -978,6 +908,17 @@ __device__ __forceinline__ void gemm_sparse(const StepArgs& a, int* li, int nz, 
     }
 }
 
+// acc += Delta_{t-1} Sigma_{SB(t-1), tile}; PLANES: of Delta (code differences: 1).
+template <int PLANES, bool TAIL>
+__device__ __forceinline__ void gemm_products(const StepArgs& a, int64_t row0, int64_t col0, uint32_t* lds,
+                                              f32x16 (&acc)[2][2])
+{
+    const XRowQ<256, PLANES, TAIL> A(a.dprev, a.S, a.q, row0, a.psbw);
+    const XRowQ<256, 3, TAIL> B(a.Sigma + a.psb, a.p, a.p, col0, a.psbw);
+    nt_tile_x3_full<PLANES == 1, PLANES == 1 ? 3 : 6>(A, row0, B, col0,
+                                                      cdiv(a.psbw, 2 * kX3KC) * (2 * kX3KC), lds, acc);
+}
+
 __device__ __forceinline__ void gemm_role(const StepArgs& a, float* lds, int64_t t)
 {
     const int64_t tm = t / a.tiles_n, tn = t % a.tiles_n;
@@ -1002,34 +943,24 @@ __device__ __forceinline__ void gemm_role(const StepArgs& a, float* lds, int64_t
         const RowOp Bo{a.Sigma + a.psb, a.p, a.p, a.psbw, a.sig_vec4 != 0};
         nt_tile(A, row0, Bo, col0, a.psbw, lds, acc);
     } else {
-        // split bf16 products (nt_x3.h); Delta rows are 16-byte aligned (stride S)
-        const XRowQ<256, 3> Bo{a.Sigma + a.psb, a.p, a.p, a.psbw};
+        // split bf16 products (nt_x3.h); code differences are exact in bf16: three exact
+        // products with Sigma's planes
         uint32_t* l32 = reinterpret_cast<uint32_t*>(lds);
-        const bool full =
-            a.sig_vec4 && row0 + kTile <= a.q && col0 + kTile <= a.p && a.psbw % (2 * kX3KC) == 0;
-        if (a.intd) {
-            // code differences are exact in bf16: three exact products with Sigma's planes
-            const XRowQ<256, 1> A{a.dprev, a.S, a.q, a.psbw};
-            if (full)
-                nt_tile_x3_full<true, 3>(A, row0, Bo, col0, a.psbw, l32, acc);
-            else
-                nt_tile_x3_edge<3>(A, row0, Bo, col0, a.psbw, l32, acc);
-        } else {
-            const XRowQ<256, 3> A{a.dprev, a.S, a.q, a.psbw};
-            if (full)
-                nt_tile_x3_full(A, row0, Bo, col0, a.psbw, l32, acc);
-            else
-                nt_tile_x3_edge(A, row0, Bo, col0, a.psbw, l32, acc);
-        }
+        if (a.psbw % (2 * kX3KC) == 0)
+            a.intd ? gemm_products<1, false>(a, row0, col0, l32, acc)
+                   : gemm_products<3, false>(a, row0, col0, l32, acc);
+        else
+            a.intd ? gemm_products<1, true>(a, row0, col0, l32, acc)
+                   : gemm_products<3, true>(a, row0, col0, l32, acc);
     }
     // R's tile is fetched before the accumulators pass through LDS, which
     // hides part of its latency
     TileRM rv;
-    tile_load_rm(a.R, a.p, a.q, a.p, row0, col0, a.r_vec4 != 0, rv);
+    tile_load_rm(a.R, a.p, a.q, a.p, row0, col0, rv);
     acc_to_lds(acc, lds);                                // the K loop ended with a barrier
     __syncthreads();
     // code differences: R += s_i (D Sigma)_i
-    tile_add_store_rm(a.R, a.p, a.q, a.p, row0, col0, a.r_vec4 != 0, rv, lds, ex0, ex1,
+    tile_add_store_rm(a.R, a.p, a.q, a.p, row0, col0, rv, lds, ex0, ex1,
                       a.intd ? a.scale : nullptr);
 }
 
@@ -1057,11 +988,15 @@ __global__ __launch_bounds__(256, 2) void cd_step_kernel(StepArgs a)
 // A sweep from valid codes runs row by row (cd_rows.hip) when few coordinates
 // move.  That is known on the device only: for the first sweeps of a call both
 // forms are enqueued, and a count over a sample of rows, taken before the
-// sweep, decides which of them does the work.  From the fourth sweep from What =
-// W on the row form was the faster one on every layer measured, and each unused
-// blocked sweep costs about 85 us of empty launches (4096 columns), so the later
-// sweeps are not given the choice.
-constexpr int kMaxOptional = 4;          // sweeps 0 .. 3 of a call
+// sweep, decides which of them does the work.  An unused blocked sweep costs
+// about 2.9 us per empty launch (50 us at 4096 columns), so the choice is not
+// offered for ever: from the fourth sweep after What = W on the row form was the
+// faster one on every layer of up to 4096 x 4096 measured; strongly coupled large
+// ones move 3% of their codes for longer (8192 x 6144, rho = 0.9: the fifth sweep
+// takes 5.2 ms row by row, 3.9 ms blocked), and there the launches weigh less.
+constexpr int kMaxOptional = 8;          // sweeps 0 .. 7 of a call
+constexpr int kFewOptional = 4;
+constexpr double kManyWork = 1.5e11;     // q p^2
 constexpr int kMovingWord = 16;          // their counts, in the status region
 static_assert((kMovingWord + kMaxOptional) * sizeof(int) <= kStatusBytes, "counts fit");
 
@@ -1195,7 +1130,6 @@ qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, in
     base.S = S;
     base.maxq = (float)((1 << bits) - 1);
     base.sig_vec4 = (aligned16(Sigma) && p % 4 == 0) ? 1 : 0;
-    base.r_vec4 = (aligned16(R) && p % 4 == 0) ? 1 : 0;
     base.fp32 = (flags & QE_CD_FP32) ? 1 : 0;
     base.dense = (flags & QE_CD_DENSE) ? 1 : 0;
     base.fpart = fpart;
@@ -1207,7 +1141,8 @@ qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, in
     const double* const f0 = f_prev;
     const bool rows = !base.dense && !base.fp32 && period == 0 && cd_rows_fits(p);
     const int limit = rows ? cd_rows_limit(q, p) : -1;
-    const int max_optional = limit >= 0 ? kMaxOptional : 0;
+    const bool large = (double)q * (double)p * (double)p >= kManyWork;
+    const int max_optional = limit < 0 ? 0 : large ? kMaxOptional : kFewOptional;
     int opt0 = -1;                       // first sweep from valid codes (with rows)
     for (int sw = 0; sw < sweeps; ++sw) {
         const int k = sw + 1;

@@ -35,6 +35,7 @@ constexpr int kX3LdsDw = 4 * kX3OpDw;            // A and B, double buffered: 49
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2a4 __attribute__((ext_vector_type(2), aligned(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -105,49 +106,37 @@ struct X3Row {
     __device__ inline void store(uint32_t* op, const X3Stage& st) const { x3_store_row8(op, st); }
 };
 
-// Row-major operand whose values are exact in bf16 (e.g. small integers: the
-// code differences of the CD block update), staged as its h plane only; it
-// pairs with the three planes of the other operand (x3_mfma_stage<3>).
-struct X1Row : X3Row {
-    __device__ inline void store(uint32_t* op, const X3Stage& st) const
-    {
-        const int t = threadIdx.x;
-        u32x4 h;
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            h[u] = __builtin_bit_cast(uint32_t, __builtin_convertvector(
-                (f32x2){st.v[u >> 1][2 * (u & 1)], st.v[u >> 1][2 * (u & 1) + 1]}, bf16x2));
-        *reinterpret_cast<u32x4*>(op + x3_addr(t >> 1, t & 1, 0)) = h;
-    }
-};
-
 // Row-major operand staged by four lanes per row: with NT threads, thread t
 // holds rows t / 4 and t / 4 + NT / 4 at k = 4 (t % 4) .. +3, so that each
 // 16-byte load instruction of a wave covers 16 rows of 64 contiguous bytes
 // (half as many cache lines per instruction as two lanes per row).  NT / 2
 // rows per stage; PLANES = 3 stores h, m and l, PLANES = 1 only h (values
 // exact in bf16, such as the code differences of the CD block update).
-template <int NT, int PLANES>
+// Any shape: rows from `rows` on repeat the last one (their results are not
+// stored), rows need no 16-byte alignment, and with TAIL columns from kvalid on
+// read as 0 (the test is uniform across the workgroup).
+template <int NT, int PLANES, bool TAIL>
 struct XRowQ {
-    const float* base;
-    int64_t ld, rows, kvalid;
-    __device__ inline void load_full(int64_t row0, int64_t k0, X3Stage& st) const
+    const float* src[2];          // this thread's rows, at its four columns of stage 0
+    int64_t kvalid;
+    __device__ inline XRowQ(const float* base, int64_t ld, int64_t rows, int64_t row0, int64_t kv) : kvalid(kv)
     {
         const int t = threadIdx.x;
-        const float* src = base + (row0 + (t >> 2)) * ld + k0 + 4 * (t & 3);
-        st.v[0] = *reinterpret_cast<const f32x4*>(src);
-        st.v[1] = *reinterpret_cast<const f32x4*>(src + (NT / 4) * ld);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            src[h] = base + min(row0 + (t >> 2) + h * (NT / 4), rows - 1) * ld + 4 * (t & 3);
     }
-    __device__ inline void load(int64_t row0, int64_t k0, X3Stage& st) const
+    __device__ inline void load_full(int64_t, int64_t k0, X3Stage& st) const
     {
-        const int t = threadIdx.x;
-        const int64_t k = k0 + 4 * (t & 3);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const int64_t r = row0 + (t >> 2) + h * (NT / 4);
+            if (!TAIL || k0 + kX3KC <= kvalid) {
+                st.v[h] = *reinterpret_cast<const f32x4a4*>(src[h] + k0);
+            } else {
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                st.v[h][u] = (r < rows && k + u < kvalid) ? base[r * ld + k + u] : 0.f;
+                for (int u = 0; u < 4; ++u)
+                    st.v[h][u] = k0 + 4 * (threadIdx.x & 3) + u < kvalid ? src[h][k0 + u] : 0.f;
+            }
         }
     }
     __device__ inline void store(uint32_t* op, const X3Stage& st) const
@@ -290,8 +279,7 @@ __device__ __forceinline__ void x3_mfma_stage(const uint32_t* sA, const uint32_t
 // LDS store instructions of one operand's stage: the four-lanes-per-row
 // loaders store 8-byte pieces (two per plane), the others 16-byte ones.
 template <class O> struct X3Writes { static constexpr int value = 3; };
-template <> struct X3Writes<X1Row> { static constexpr int value = 1; };
-template <int NT, int PL> struct X3Writes<XRowQ<NT, PL>> { static constexpr int value = 2 * PL; };
+template <int NT, int PL, bool TL> struct X3Writes<XRowQ<NT, PL, TL>> { static constexpr int value = 2 * PL; };
 template <class O> constexpr int x3_writes() { return X3Writes<O>::value; }
 
 // Instruction order of one stage when INTERLEAVE is set: the operand reads,

@@ -275,18 +275,19 @@ __device__ inline void tile_store(float* M, int64_t ld, int64_t rows, int64_t co
 
 // Row-major view of a 128 x 128 tile for a 256-thread workgroup: thread t owns
 // the float4 at row (t >> 5) + 8 j, columns 4 (t & 31) .. +3, for j = 0..15.
-// One base address per thread keeps a prefetched tile cheap in registers.
+// One base address per thread keeps a prefetched tile cheap in registers.  Rows
+// need no 16-byte alignment.
 struct TileRM { f32x4 v[16]; };
 
 __device__ inline void tile_load_rm(const float* M, int64_t ld, int64_t rows, int64_t cols,
-                                    int64_t row0, int64_t col0, bool vec4, TileRM& T)
+                                    int64_t row0, int64_t col0, TileRM& T)
 {
     const int t = threadIdx.x;
     const int64_t r0 = row0 + (t >> 5), c0 = col0 + 4 * (t & 31);
-    if (vec4 && row0 + kTile <= rows && col0 + kTile <= cols) {
+    if (row0 + kTile <= rows && col0 + kTile <= cols) {
         const float* base = M + r0 * ld + c0;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) T.v[j] = *reinterpret_cast<const f32x4*>(base + 8 * j * ld);
+        for (int j = 0; j < 16; ++j) T.v[j] = *reinterpret_cast<const f32x4a4*>(base + 8 * j * ld);
         return;
     }
 #pragma unroll
@@ -303,14 +304,14 @@ __device__ inline void tile_load_rm(const float* M, int64_t ld, int64_t rows, in
 // multiply-add; without it the sum is T + acc.
 constexpr int kAccStride = kTile + 4;
 __device__ inline void tile_add_store_rm(float* M, int64_t ld, int64_t rows, int64_t cols,
-                                         int64_t row0, int64_t col0, bool vec4, const TileRM& T,
+                                         int64_t row0, int64_t col0, const TileRM& T,
                                          const float* accLds, int64_t ex0 = 0, int64_t ex1 = 0,
                                          const float* rowscale = nullptr)
 {
     const int t = threadIdx.x;
     const int lr = t >> 5, lc = 4 * (t & 31);
     const int64_t r0 = row0 + lr, c0 = col0 + lc;
-    if (vec4 && row0 + kTile <= rows && col0 + kTile <= cols &&
+    if (row0 + kTile <= rows && col0 + kTile <= cols &&
         (ex1 <= col0 || ex0 >= col0 + kTile)) {
         float* base = M + r0 * ld + c0;
 #pragma unroll
@@ -321,9 +322,9 @@ __device__ inline void tile_add_store_rm(float* M, int64_t ld, int64_t rows, int
                 f32x4 o;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) o[u] = fmaf(sc, a[u], T.v[j][u]);
-                *reinterpret_cast<f32x4*>(base + 8 * j * ld) = o;
+                *reinterpret_cast<f32x4a4*>(base + 8 * j * ld) = o;
             } else {
-                *reinterpret_cast<f32x4*>(base + 8 * j * ld) = T.v[j] + a;
+                *reinterpret_cast<f32x4a4*>(base + 8 * j * ld) = T.v[j] + a;
             }
         }
         return;

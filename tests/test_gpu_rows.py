@@ -5,6 +5,7 @@ of one wave's columns (1024) and of its range (16384), and where the choice
 between this form and the blocked one is made on the device."""
 import numpy as np
 import pytest
+import torch
 
 import synth
 from parity import dev, host, teacher_forced
@@ -75,3 +76,28 @@ def test_fixed_point_and_no_objective(qe, oracle):
     before = host(R).copy()
     qe.cd_sweep(Wd, Sd, 4, sc, ze, Wh, codes, R, 2, flags=qe.QE_R_VALID | qe.QE_CODES_VALID)
     assert np.array_equal(host(R), before) and np.array_equal(host(codes), g["codes"])
+
+
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("q,p", [(17, 257), (150, 301), (129, 640), (260, 1027)])
+def test_alignment_changes_nothing(qe, oracle, q, p, dense):
+    """Arrays whose rows are not 16-byte aligned (an odd p, bases 4 bytes off), with
+    NaN around them that any read past their ends would pick up: bitwise the
+    results of aligned bases, in the blocked form and row by row."""
+    W, X = layer(q, p, 2 * p, 54, corr=0.5)
+    S32 = oracle.damp(oracle.gram(X), 0.01).astype(np.float32)
+    scale, zero = oracle.grid_minmax(W, 4)
+    flag = qe.QE_CD_DENSE if dense else 0
+    want = gpu_cd(qe, W, S32, 4, scale, zero, 3, per_sweep=False, extra=flag)
+
+    def off(a):
+        buf = torch.full((a.size + 67,), float("nan"), device="cuda")
+        v = buf[1:1 + a.size].view(*a.shape)
+        v.copy_(dev(a))
+        return v
+    Wh, R = off(np.zeros_like(W)), off(np.zeros_like(W))
+    cbuf = torch.zeros(q * p + 8, dtype=torch.uint8, device="cuda")
+    codes = cbuf[1:1 + q * p].view(q, p)
+    qe.cd_sweep(off(W), off(S32), 4, dev(scale), dev(zero), Wh, codes, R, 3, flags=qe.QE_INIT_FROM_W | flag)
+    assert np.array_equal(host(Wh), want["What"]) and np.array_equal(host(R), want["R"])
+    assert np.array_equal(host(codes).astype(np.int32), want["codes"])
