@@ -494,11 +494,181 @@ __global__ __launch_bounds__(256) void power_last_kernel(const double* part, int
     if (threadIdx.x == 0) put_hist(lam_hist, slot, t[0], t[1], t[2]);
 }
 
+// ---- the same with Sigma kept on the chip (p <= 4096)
+// One launch runs a whole batch of iterations: workgroup b holds rows 8 RW b .. 8 RW b
+// + 8 RW - 1 of Sigma in registers (RW rows per wavefront, 4 NC values of each per
+// lane; RW = 2 above 2048 channels), so that an iteration moves only y.  y travels between the workgroups as 64-bit words
+// of a value and the iteration that made it, stored and polled with agent-scope
+// atomics: the word carries its own flag, so no other ordering is needed.  Two
+// buffers alternate; a workgroup writes iteration k + 1 only after it has read all of
+// k, when every other one has done with k - 1.  The launch is cooperative (all
+// workgroups resident), and a wait that lasts kMaxPolls polls gives up: the batch
+// then reports it and the call falls back to a launch per iteration.
+// Bound by the exchange of y (about 2.7 us an iteration) and, at 4096, by the
+// conversions of the fp64 products: 12.7 -> 6.4 us an iteration at 4096 (Sigma, 67 MB,
+// streamed before), 6.7 -> 2.0 us at 1025, the call 5.0 -> 2.5 ms and 3.2 -> 1.0 ms.
+constexpr int64_t kChipMaxP = 4096;          // 256 workgroups of 128 values per lane
+constexpr int kMaxPolls = 1 << 20;
+
+__global__ __launch_bounds__(256) void power_clear_kernel(uint64_t* y, int64_t n, int* gave_up)
+{
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t < n) y[t] = 0;
+    if (t == 0) *gave_up = 0;
+}
+
+template <int NC, int RW>
+__global__ __launch_bounds__(512, 1) void power_batch_kernel(const float* Sigma, int p, uint64_t* ybuf, int it0,
+                                                          int iters, double* part, int* gave_up)
+{
+    __shared__ __attribute__((aligned(16))) float y[256 * NC];
+    __shared__ double wsum[8], wpart[8][3];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r0 = RW * (8 * (int)blockIdx.x + wave);
+    f32x4 sv[RW][NC];
+#pragma unroll
+    for (int rr = 0; rr < RW; ++rr)
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            const int c = 256 * i + 4 * lane;
+            const float* src = Sigma + (int64_t)min(r0 + rr, p - 1) * p + c;
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+            if (c + 4 <= p) {
+                v = *reinterpret_cast<const f32x4a4*>(src);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (c + e < p) v[e] = src[e];
+            }
+            sv[rr][i] = v;
+        }
+    for (int k = 0; k < iters; ++k) {
+        const uint32_t tag = (uint32_t)(it0 + k);        // y of iteration tag - 1
+        const uint64_t* yin = ybuf + (tag & 1) * (int64_t)kChipMaxP;
+        uint64_t* yout = ybuf + ((tag + 1) & 1) * (int64_t)kChipMaxP;
+        // this thread's values: all loads of a poll in flight together
+        constexpr int NV = (256 * NC + 511) / 512;
+        uint64_t w[NV];
+        int late = 0;
+        if (tag != 0) {
+            int polls = 0;
+            do {
+                late = 0;
+#pragma unroll
+                for (int v = 0; v < NV; ++v) {
+                    const int c = threadIdx.x + 512 * v;
+                    w[v] = (uint64_t)tag << 32;
+                    if (c < p) w[v] = __hip_atomic_load(yin + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+#pragma unroll
+                for (int v = 0; v < NV; ++v) late |= (uint32_t)(w[v] >> 32) != tag;
+            } while (late && ++polls < kMaxPolls);
+        }
+        double sq = 0.0;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const int c = threadIdx.x + 512 * v;
+            const float val = tag != 0 ? __uint_as_float((uint32_t)w[v]) : c < p ? 1.f : 0.f;
+            if (c < 256 * NC) y[c] = val;
+            sq += (double)val * (double)val;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
+        if (lane == 0) wsum[wave] = sq;
+        if (__syncthreads_or(late)) {                    // uniform: the workgroup leaves
+            if (threadIdx.x == 0) atomicExch(gave_up, 1);
+            return;
+        }
+        double yy = 0.0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) yy += wsum[w];
+        const double inv = yy > 0.0 ? 1.0 / sqrt(yy) : 0.0;
+        double acc[RW] = {};
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            const f32x4 yv = *reinterpret_cast<const f32x4*>(y + 256 * i + 4 * lane);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int rr = 0; rr < RW; ++rr) {
+                    // (opaque, or the conversions to fp64 would be hoisted out of the
+                    // loop, twice the registers)
+                    float a = sv[rr][i][e];
+                    asm volatile("" : "+v"(a));
+                    acc[rr] += (double)a * (double)yv[e];
+                }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+            for (int rr = 0; rr < RW; ++rr) acc[rr] += __shfl_xor(acc[rr], o, 64);
+        if (lane == 0) {
+            double pyy = 0.0, pvy = 0.0, pvv = 0.0;
+#pragma unroll
+            for (int rr = 0; rr < RW; ++rr) {
+                if (r0 + rr >= p) continue;
+                const double yd = acc[rr] * inv;         // (S v)_r in fp64
+                __hip_atomic_store(yout + r0 + rr,
+                                   ((uint64_t)(tag + 1) << 32) | __float_as_uint((float)yd),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const double vr = (double)y[r0 + rr] * inv;
+                pyy += yd * yd;
+                pvy += vr * yd;
+                pvv += vr * vr;
+            }
+            wpart[wave][0] = pyy;
+            wpart[wave][1] = pvy;
+            wpart[wave][2] = pvv;
+        }
+        __syncthreads();                                 // y, wsum and wpart are free again below
+        if (threadIdx.x < 3) {
+            double t = 0.0;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) t += wpart[w][threadIdx.x];
+            part[((int64_t)k * gridDim.x + blockIdx.x) * 3 + threadIdx.x] = t;
+        }
+    }
+}
+
+// Quotients and radii of a batch: workgroup k sums iteration k's partials.
+__global__ __launch_bounds__(256) void power_hist_kernel(const double* part, int nwg, double* lam_hist)
+{
+    __shared__ double sh[4][3];
+    const double* src = part + (int64_t)blockIdx.x * nwg * 3;
+    Partials3 s;
+    s.early(src, nwg);
+    double t[3];
+    s.sum(src, nwg, sh, t);
+    if (threadIdx.x == 0) put_hist(lam_hist, blockIdx.x, t[0], t[1], t[2]);
+}
+
+static int64_t chip_wgs(int64_t p) { return cdiv(p, p > 2048 ? 16 : 8); }
+
 size_t lambda_ws_bytes(int64_t p)
 {
     const int64_t nwg = cdiv(p, kSymvRows);
-    return kStatusBytes + 2 * align256(sizeof(float) * p) +
-           2 * align256(sizeof(double) * 3 * nwg) + align256(sizeof(double) * 2 * kLambdaCheck);
+    size_t b = kStatusBytes + 2 * align256(sizeof(float) * p) +
+               2 * align256(sizeof(double) * 3 * nwg) + align256(sizeof(double) * 2 * kLambdaCheck + 8);
+    if (p <= kChipMaxP)
+        b += align256(sizeof(uint64_t) * 2 * kChipMaxP) +
+             align256(sizeof(double) * 3 * chip_wgs(p) * kLambdaCheck);
+    return b;
+}
+
+// Cooperative launch of one batch; false if the runtime does not take it.
+static bool launch_chip_batch(const float* Sigma, int p, uint64_t* ybuf, int it0, int iters, double* part,
+                              int* gave_up, hipStream_t s)
+{
+    const void* f = p <= 512    ? reinterpret_cast<const void*>(power_batch_kernel<2, 1>)
+                    : p <= 1024 ? reinterpret_cast<const void*>(power_batch_kernel<4, 1>)
+                    : p <= 2048 ? reinterpret_cast<const void*>(power_batch_kernel<8, 1>)
+                    : p <= 3072 ? reinterpret_cast<const void*>(power_batch_kernel<12, 2>)
+                                : reinterpret_cast<const void*>(power_batch_kernel<16, 2>);
+    void* args[] = {&Sigma, &p, &ybuf, &it0, &iters, &part, &gave_up};
+    if (hipLaunchCooperativeKernel(f, dim3((unsigned)chip_wgs(p)), dim3(512), args, 0, s) == hipSuccess)
+        return true;
+    (void)hipGetLastError();
+    return false;
 }
 
 qe_status launch_lambda(const float* Sigma, int64_t p, int max_iters, float tol, float* out,
@@ -508,28 +678,53 @@ qe_status launch_lambda(const float* Sigma, int64_t p, int max_iters, float tol,
     const int64_t nwg = cdiv(p, kSymvRows);
     float* y[2] = {w.take<float>(p), w.take<float>(p)};
     double* part[2] = {w.take<double>(3 * nwg), w.take<double>(3 * nwg)};
-    double* hist = w.take<double>(2 * kLambdaCheck);      // (rho, radius^2) per iteration
+    double* hist = w.take<double>(2 * kLambdaCheck + 1);  // (rho, radius^2) per iteration; gave_up
+    int* const gave_up = reinterpret_cast<int*>(hist + 2 * kLambdaCheck);
+    bool chip = p <= kChipMaxP;
+    uint64_t* ybuf = nullptr;
+    double* cpart = nullptr;
+    if (chip) {
+        ybuf = w.take<uint64_t>(2 * kChipMaxP);
+        cpart = w.take<double>(3 * chip_wgs(p) * kLambdaCheck);
+        hipLaunchKernelGGL(power_clear_kernel, dim3((unsigned)cdiv(2 * kChipMaxP, 256)), dim3(256), 0, s,
+                           ybuf, 2 * kChipMaxP, gave_up);
+    }
     const int vec4 = (aligned16(Sigma) && p % 4 == 0) ? 1 : 0;
     double last = 0.0, prev = 0.0, last_r2 = 0.0;
     int it = 0, cur = 0;
     while (it < max_iters) {
         const int batch = std::min(kLambdaCheck, max_iters - it);
-        for (int b = 0; b < batch; ++b) {
-            const int nxt = cur ^ 1;
-            hipLaunchKernelGGL(power_step_kernel, dim3((unsigned)nwg), dim3(256), 0, s, Sigma, p,
-                               y[cur], part[cur], it + b == 0 ? 1 : 0, vec4, y[nxt], part[nxt],
-                               hist, b);
-            cur = nxt;
+        if (chip && !launch_chip_batch(Sigma, (int)p, ybuf, it, batch, cpart, gave_up, s)) {
+            chip = false;
+            it = 0;
+            last = 0.0;
+            continue;
         }
-        hipLaunchKernelGGL(power_last_kernel, dim3(1), dim3(256), 0, s, part[cur], (int)nwg, hist,
-                           batch - 1);
+        if (chip) {
+            hipLaunchKernelGGL(power_hist_kernel, dim3((unsigned)batch), dim3(256), 0, s, cpart,
+                               (int)chip_wgs(p), hist);
+        } else {
+            for (int b = 0; b < batch; ++b) {
+                const int nxt = cur ^ 1;
+                hipLaunchKernelGGL(power_step_kernel, dim3((unsigned)nwg), dim3(256), 0, s, Sigma, p,
+                                   y[cur], part[cur], it + b == 0 ? 1 : 0, vec4, y[nxt], part[nxt],
+                                   hist, b);
+                cur = nxt;
+            }
+            hipLaunchKernelGGL(power_last_kernel, dim3(1), dim3(256), 0, s, part[cur], (int)nwg, hist,
+                               batch - 1);
+        }
         it += batch;
         if (hipGetLastError() != hipSuccess) return QE_ERR_HIP;
-        double h[2 * kLambdaCheck];
-        if (hipMemcpyAsync(h, hist, sizeof(double) * 2 * batch, hipMemcpyDeviceToHost, s) !=
-            hipSuccess)
-            return QE_ERR_HIP;
+        double h[2 * kLambdaCheck + 1];
+        if (hipMemcpyAsync(h, hist, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess) return QE_ERR_HIP;
         if (hipStreamSynchronize(s) != hipSuccess) return QE_ERR_HIP;
+        if (chip && *reinterpret_cast<const int*>(h + 2 * kLambdaCheck) != 0) {
+            chip = false;                                // a wait gave up: start over, launch by launch
+            it = 0;
+            last = 0.0;
+            continue;
+        }
         // the first iteration of the batch whose quotient moved by <= tol relative
         bool done = false;
         for (int b = 0; b < batch && !done; ++b) {

@@ -242,3 +242,46 @@ def test_lemma3_descent_with_the_library_lambda(qe, oracle):
         assert g[2 * k + 1] <= g[2 * k] * (1 + 1e-6), f"IHT step {k + 1}"
         if k:
             assert g[2 * k] <= g[2 * k - 1] * (1 + 1e-6), f"CD step {k + 1}"
+
+
+@pytest.mark.parametrize("p", [1, 2, 7, 9, 257, 512, 513, 1025, 2048, 2049, 3071, 4096, 4097])
+def test_lambda_max_sizes(qe, p):
+    """The rows and columns a workgroup keeps on the chip, at the edges of their
+    counts and past the largest (4097: a launch per iteration), against the fp64
+    power method with the same stop rule.  Bound as in the stop-rule test: y is
+    rounded to fp32 between iterations."""
+    X = synth.correlated_activations(p, 96, 0.9, 5, out_channels=max(1, p // 200), out_mult=8.0)
+    S = (X.astype(np.float64) @ X.T.astype(np.float64)).astype(np.float32)
+    buf = torch.full((p * p + 9,), float("nan"), device="cuda")
+    Sd = buf[1:1 + p * p].view(p, p)
+    Sd.copy_(dev(S))
+    lam = qe.lambda_max(Sd, max_iters=70, tol=1e-5)
+    rho, res = _power_method(S, 70, 1e-5)
+    assert lam == pytest.approx(rho + res, rel=2e-6)
+    ws = qe.workspace(qe.load().qe_lambda_workspace_size(p), "cuda")
+    assert qe.lambda_max(Sd, max_iters=70, tol=1e-5, ws=ws) == lam
+    assert qe.lambda_max(Sd, max_iters=70, tol=1e-5, ws=ws) == lam      # stale words in ws
+
+
+def test_lambda_max_two_threads(qe):
+    """Two host threads with a stream and a workspace each: the same values as one
+    after the other."""
+    import threading
+    mats = []
+    for k, p in enumerate((1500, 4000)):
+        X = synth.correlated_activations(p, 96, 0.9, 6 + k, out_channels=5, out_mult=8.0)
+        mats.append(dev((X.astype(np.float64) @ X.T.astype(np.float64)).astype(np.float32)))
+    alone = [qe.lambda_max(S) for S in mats]
+    got = [None, None]
+
+    def work(k):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            got[k] = [qe.lambda_max(mats[k], stream=s) for _ in range(4)]
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert got == [[alone[0]] * 4, [alone[1]] * 4]
