@@ -570,11 +570,14 @@ static int64_t chan_slices(int64_t p, int64_t n)
         1, std::min<int64_t>(std::min<int64_t>(512, 2048 / blocks), std::max(cdiv(n, 256), few)));
 }
 
-// Workspace of the channel exponents: p ints and the token-major partials.
+// Workspace of the channel exponents: p ints and the token-major partials (room for
+// as many slices as with 1024 channels a workgroup, the layout's documented size).
 static size_t chan_ws_bytes(int64_t p, int64_t n)
 {
+    const int64_t wide = std::max<int64_t>(
+        1, std::min<int64_t>(std::min<int64_t>(512, 2048 / cdiv(p, 1024)), cdiv(n, 256)));
     return align256((size_t)p * sizeof(int)) +
-           align256((size_t)chan_slices(p, n) * p * sizeof(float));
+           align256((size_t)std::max(wide, chan_slices(p, n)) * p * sizeof(float));
 }
 
 // Number of token splits, or 0 for the two-level direct mode.
