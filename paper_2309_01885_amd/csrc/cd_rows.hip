@@ -90,7 +90,10 @@ __device__ __forceinline__ void apply_move(f32x4 (&L)[G], const float* srow, int
 }
 
 // One group of 256 columns of the wave's turn.  Returns the number of moves so far.
-template <int G, int g, bool FULL>
+// KEEP: the group's codes stay unpacked over its moves (four more registers, which
+// cost workgroups of many waves one of two places on a CU: 2.3 -> 2.9 ms for a
+// sweep of 0.7% at 4096 x 11008).
+template <int G, int g, bool FULL, bool KEEP>
 __device__ __forceinline__ int take_group(const RowsArgs& a, f32x4 (&L)[G], uint32_t (&code)[G], int c0,
                                           int wcol, float s, float inv_s, int2* list, double& f, int cnt)
 {
@@ -98,8 +101,13 @@ __device__ __forceinline__ int take_group(const RowsArgs& a, f32x4 (&L)[G], uint
     const int n = (int)a.p;
     if (!FULL && wcol + 256 * g >= n) return cnt;
     f32x4 u = load4<FULL>(a.inv_d, c0 + 256 * g, n);
+    auto unpack = [&](int e) { return (float)((code[g] >> (8 * e)) & 0xffu); };
+    float kc[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) u[e] *= inv_s;
+    for (int e = 0; e < 4; ++e) {
+        u[e] *= inv_s;
+        if constexpr (KEEP) kc[e] = unpack(e);
+    }
     // the columns still to be taken: inside the row, behind the last move
     uint64_t open[4];
 #pragma unroll
@@ -109,46 +117,54 @@ __device__ __forceinline__ int take_group(const RowsArgs& a, f32x4 (&L)[G], uint
         uint64_t m[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const float kc = (float)((code[g] >> (8 * e)) & 0xffu);
             // Lemma 1's minimiser on the grid axis, its nearest level; a valid,
             // equally near current level is kept (Sec. 3.3)
-            const float t = fmaf(-L[g][e], u[e], kc);
+            if constexpr (!KEEP) kc[e] = unpack(e);
+            const float t = fmaf(-L[g][e], u[e], kc[e]);
             const float kn = __builtin_amdgcn_fmed3f(rintf(t), 0.f, a.maxq);
-            d[e] = kn - kc;
-            m[e] = __ballot(d[e] != 0.f && !(fabsf(t - kc) <= fabsf(t - kn))) & open[e];
+            d[e] = kn - kc[e];
+            m[e] = __ballot(!(fabsf(t - kc[e]) <= fabsf(t - kn))) & open[e];
         }
         const uint64_t any = m[0] | m[1] | m[2] | m[3];
-        if (any == 0) return cnt;
+        if (any == 0) break;
         const int ls = __builtin_ctzll(any);
         const int es = (m[0] >> ls) & 1 ? 0 : (m[1] >> ls) & 1 ? 1 : (m[2] >> ls) & 1 ? 2 : 3;
         const float dsel = es == 0 ? d[0] : es == 1 ? d[1] : es == 2 ? d[2] : d[3];
         const float dm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(dsel), ls));
         const float delta = s * dm;
         const int j = wcol + 256 * g + 4 * ls + es;
-        const uint64_t behind = (~0ull << ls) << 1;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) open[e] &= behind | (e > es ? 1ull << ls : 0ull);
-        if (list && lane == 0) list[cnt] = make_int2(j, __float_as_int(delta));
+        const uint64_t at = 1ull << ls, behind = (~0ull << ls) << 1;
         const float r0 = es == 0 ? L[g][0] : es == 1 ? L[g][1] : es == 2 ? L[g][2] : L[g][3];
+        const float mine = lane == ls ? dm : 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            open[e] &= behind | (e > es ? at : 0ull);
+            if constexpr (KEEP) kc[e] += e == es ? mine : 0.f;
+        }
+        if constexpr (!KEEP) code[g] += (uint32_t)((int)mine << (8 * es));
+        if (list && lane == 0) list[cnt] = make_int2(j, __float_as_int(delta));
         apply_move<G, FULL>(L, a.Sigma + (int64_t)j * a.p, c0, n, delta);
         const float r1 = es == 0 ? L[g][0] : es == 1 ? L[g][1] : es == 2 ? L[g][2] : L[g][3];
-        if (lane == ls) {
-            code[g] += (uint32_t)((int)dm << (8 * es));
-            // the move changes f by delta (2 R + delta Sigma_jj) = delta (R + R')
-            f += (double)delta * ((double)r0 + (double)r1);
-        }
+        // the move changes f by delta (2 R + delta Sigma_jj) = delta (R + R')
+        f += (double)(s * mine) * ((double)r0 + (double)r1);
         ++cnt;
     }
+    if constexpr (KEEP) {
+        code[g] = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) code[g] |= (uint32_t)kc[e] << (8 * e);
+    }
+    return cnt;
 }
 
 // One turn: the wave's columns in order.  Returns the number of moves.
-template <int G, bool FULL, int... g>
+template <int G, bool FULL, bool KEEP, int... g>
 __device__ __forceinline__ int take_turn(std::integer_sequence<int, g...>, const RowsArgs& a, f32x4 (&L)[G],
                                          uint32_t (&code)[G], int c0, int wcol, float s, float inv_s,
                                          int2* list, double& f)
 {
     int cnt = 0;
-    ((cnt = take_group<G, g, FULL>(a, L, code, c0, wcol, s, inv_s, list, f, cnt)), ...);
+    ((cnt = take_group<G, g, FULL, KEEP>(a, L, code, c0, wcol, s, inv_s, list, f, cnt)), ...);
     return cnt;
 }
 
@@ -197,8 +213,8 @@ __global__ __launch_bounds__(MULTI ? 1024 : 64) void cd_rows_kernel(RowsArgs a)
         for (int w = 0; w < W; ++w, turn ^= 1) {
             int2* li = MULTI ? list[turn] : nullptr;
             if (wave == w) {
-                const int cnt = full ? take_turn<G, true>(groups, a, L, code, c0, wcol, s, inv_s, li, f)
-                                     : take_turn<G, false>(groups, a, L, code, c0, wcol, s, inv_s, li, f);
+                const int cnt = full ? take_turn<G, true, !MULTI>(groups, a, L, code, c0, wcol, s, inv_s, li, f)
+                                     : take_turn<G, false, !MULTI>(groups, a, L, code, c0, wcol, s, inv_s, li, f);
                 if (lane == 0) count[turn] = cnt;
             }
             __syncthreads();
@@ -263,22 +279,32 @@ __global__ __launch_bounds__(MULTI ? 1024 : 64) void cd_rows_kernel(RowsArgs a)
 }
 
 // obj[k] = the objective before sweep k + its change, for the sweeps of a
-// cd_rows_kernel launch; each sweep's changes are summed over the rows in a fixed
-// order.  f0: the objective before the call's first sweep (null: 0).
-__global__ __launch_bounds__(256) void rows_objective_kernel(RowsArgs a, const double* f0, double* obj,
-                                                             int stride)
+// cd_rows_kernel launch.  Workgroup b sums sweep k0 + b's changes over the rows in a
+// fixed order, in place of the first row's; the second kernel adds them up.  f0: the
+// objective before the call's first sweep (null: 0).
+__global__ __launch_bounds__(256) void rows_sum_kernel(RowsArgs a)
 {
     if (failed(a.status)) return;
+    const int k = a.k0 + blockIdx.x;
+    if (k < max(a.k0, first_sweep(a.moving, a.opt0, a.opt1, a.limit))) return;
+    __shared__ double sh[256];
+    double* part = a.fpart + (int64_t)blockIdx.x * a.q;
+    double acc = 0.0;
+#pragma unroll 4
+    for (int64_t e = threadIdx.x; e < a.q; e += 256) acc += part[e];
+    const double t = block_sum_f64(acc, sh);
+    if (threadIdx.x == 0) part[0] = t;
+}
+
+__global__ void rows_objective_kernel(RowsArgs a, const double* f0, double* obj, int stride)
+{
+    if (failed(a.status) || threadIdx.x != 0) return;
     const int start = max(a.k0, first_sweep(a.moving, a.opt0, a.opt1, a.limit));
     if (start >= a.k1) return;
-    __shared__ double sh[256];
     double f = start > 0 ? obj[(int64_t)(start - 1) * stride] : (f0 ? *f0 : 0.0);
     for (int k = start; k < a.k1; ++k) {
-        const double* part = a.fpart + (int64_t)(k - a.k0) * a.q;
-        double acc = 0.0;
-        for (int64_t e = threadIdx.x; e < a.q; e += blockDim.x) acc += part[e];
-        f += block_sum_f64(acc, sh);
-        if (threadIdx.x == 0) obj[(int64_t)k * stride] = f;
+        f += a.fpart[(int64_t)(k - a.k0) * a.q];
+        obj[(int64_t)k * stride] = f;
     }
 }
 
@@ -369,7 +395,10 @@ qe_status launch_cd_rows(const float* Sigma, int64_t q, int64_t p, const float* 
         else QE_ROWS(4, true);
 #undef QE_ROWS
         if (obj)
-            hipLaunchKernelGGL(rows_objective_kernel, dim3(1), dim3(256), 0, s, a, f0, obj, obj_stride);
+        {
+            hipLaunchKernelGGL(rows_sum_kernel, dim3((unsigned)(a.k1 - a.k0)), dim3(256), 0, s, a);
+            hipLaunchKernelGGL(rows_objective_kernel, dim3(1), dim3(64), 0, s, a, f0, obj, obj_stride);
+        }
         if (hipGetLastError() != hipSuccess) return QE_ERR_HIP;
     }
     return QE_OK;
