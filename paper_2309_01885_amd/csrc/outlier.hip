@@ -137,6 +137,20 @@ __global__ __launch_bounds__(256) void sel_pick_kernel(SelState* st, uint32_t* h
     for (int b = t; b < kHistBins; b += blockDim.x) hist[b] = 0u;
 }
 
+// Four consecutive values from e on (chunks start at multiples of four); those at or
+// past e1 read as 0, whose key no selection takes (in[u]: inside).
+__device__ __forceinline__ f32x4 sel_load4(const float* V, int64_t e, int64_t e1, bool (&in)[4])
+{
+#pragma unroll
+    for (int u = 0; u < 4; ++u) in[u] = e + u < e1;
+    if (in[3]) return *reinterpret_cast<const f32x4a4*>(V + e);
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < 3; ++u)
+        if (in[u]) v[u] = V[e + u];
+    return v;
+}
+
 // Per-workgroup counts of keys > tau and keys == tau over contiguous chunks.
 __global__ __launch_bounds__(256) void sel_count_kernel(const float* __restrict__ V, int64_t count,
                                                         int64_t chunk, const SelState* st,
@@ -148,10 +162,16 @@ __global__ __launch_bounds__(256) void sel_count_kernel(const float* __restrict_
     const bool want_eq = st->need_eq > 0;
     const int64_t e0 = (int64_t)blockIdx.x * chunk, e1 = min(count, e0 + chunk);
     int64_t gt = 0, eq = 0;
-    for (int64_t e = e0 + threadIdx.x; e < e1; e += blockDim.x) {
-        const uint32_t key = abs_key(V[e]);
-        gt += key > tau;
-        eq += want_eq && key == tau;
+#pragma unroll 4
+    for (int64_t e = e0 + 4 * threadIdx.x; e < e1; e += 1024) {
+        bool in[4];
+        const f32x4 v = sel_load4(V, e, e1, in);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t key = abs_key(v[u]);
+            gt += in[u] && key > tau;
+            eq += in[u] && want_eq && key == tau;
+        }
     }
     const double g = block_sum_f64((double)gt, sh);
     const double q = block_sum_f64((double)eq, sh);
@@ -213,7 +233,9 @@ __global__ __launch_bounds__(256) void sel_scan_kernel(const int64_t* cnt, int64
     }
 }
 
-// Writes the selected indices (ascending) and values, and the dense P_s(V).
+// Writes the selected indices (ascending) and values, and the dense P_s(V).  A pass
+// takes 1024 values, four consecutive ones per thread, so that its barriers and
+// ballots are shared by four (one value per thread: 59 us at 4096 x 4096).
 __global__ __launch_bounds__(256) void sel_write_kernel(const float* __restrict__ V, int64_t count,
                                                         int64_t chunk, const SelState* st,
                                                         const int64_t* off, const int64_t* adm,
@@ -222,44 +244,80 @@ __global__ __launch_bounds__(256) void sel_write_kernel(const float* __restrict_
                                                         const int* status)
 {
     if (failed(status)) return;
-    __shared__ int wsel[4], weq[4];
+    __shared__ int wsel[2][4], weq[2][4];
     const uint32_t tau = st->tau;
-    const bool want_eq = st->need_eq > 0;
+    const bool want_eq = st->need_eq > 0;            // uniform
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const int64_t e0 = (int64_t)blockIdx.x * chunk, e1 = min(count, e0 + chunk);
     int64_t pos = off[blockIdx.x];
     int64_t eq_seen = 0;
     const int64_t eq_admit = adm[blockIdx.x];
-    for (int64_t base = e0; base < e1; base += blockDim.x) {
-        const int64_t e = base + threadIdx.x;
-        const bool in = e < e1;
-        const float v = in ? V[e] : 0.f;
-        const uint32_t key = abs_key(v);
-        const bool is_gt = in && key > tau;
-        const bool is_eq = in && want_eq && key == tau;
-        // rank of this tie among the workgroup's ties so far
-        const uint64_t meq = __ballot(is_eq);
-        if (lane == 0) weq[wave] = __popcll(meq);
-        __syncthreads();
-        int eq_before = __popcll(meq & below);
-        for (int w = 0; w < wave; ++w) eq_before += weq[w];
-        int eq_tile = weq[0] + weq[1] + weq[2] + weq[3];
-        const bool sel = (is_gt || (is_eq && eq_seen + eq_before < eq_admit));
-        const uint64_t msel = __ballot(sel);
-        if (lane == 0) wsel[wave] = __popcll(msel);
-        __syncthreads();
-        int sel_before = __popcll(msel & below);
-        for (int w = 0; w < wave; ++w) sel_before += wsel[w];
-        const int sel_tile = wsel[0] + wsel[1] + wsel[2] + wsel[3];
-        if (sel && pos + sel_before < cap) {
-            idx_out[pos + sel_before] = e;
-            if (val_out) val_out[pos + sel_before] = v;
+    int turn = 0;
+    // (two sets of counts alternate, so that one barrier per exchange is enough)
+    for (int64_t base = e0; base < e1; base += 1024, turn ^= 1) {
+        const int64_t e = base + 4 * threadIdx.x;
+        bool in[4], sel[4];
+        const f32x4 v = sel_load4(V, e, e1, in);
+        uint32_t key[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            key[u] = abs_key(v[u]);
+            sel[u] = in[u] && key[u] > tau;
         }
-        if (in && dense_out) dense_out[e] = sel ? v : 0.f;
-        pos += sel_tile;
-        eq_seen += eq_tile;
+        if (want_eq) {
+            // rank of each tie among the workgroup's ties so far
+            uint64_t m[4];
+            int tot = 0, before = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                m[u] = __ballot(in[u] && key[u] == tau);
+                tot += __popcll(m[u]);
+                before += __popcll(m[u] & below);
+            }
+            if (lane == 0) weq[turn][wave] = tot;
+            __syncthreads();
+            for (int w = 0; w < wave; ++w) before += weq[turn][w];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (!(in[u] && key[u] == tau)) continue;
+                sel[u] = eq_seen + before < eq_admit;
+                ++before;
+            }
+            eq_seen += weq[turn][0] + weq[turn][1] + weq[turn][2] + weq[turn][3];
+        }
+        int tot = 0, before = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint64_t m = __ballot(sel[u]);
+            tot += __popcll(m);
+            before += __popcll(m & below);
+        }
+        if (lane == 0) wsel[turn][wave] = tot;
         __syncthreads();
+        for (int w = 0; w < wave; ++w) before += wsel[turn][w];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (!sel[u]) continue;
+            if (pos + before < cap) {
+                idx_out[pos + before] = e + u;
+                if (val_out) val_out[pos + before] = v[u];
+            }
+            ++before;
+        }
+        if (dense_out) {
+            f32x4 o;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) o[u] = sel[u] ? v[u] : 0.f;
+            if (in[3]) {
+                *reinterpret_cast<f32x4a4*>(dense_out + e) = o;
+            } else {
+#pragma unroll
+                for (int u = 0; u < 3; ++u)
+                    if (in[u]) dense_out[e + u] = o[u];
+            }
+        }
+        pos += wsel[turn][0] + wsel[turn][1] + wsel[turn][2] + wsel[turn][3];
     }
 }
 
@@ -291,7 +349,7 @@ static qe_status run_select(const float* V, int64_t count, int64_t s, SelState* 
         hipLaunchKernelGGL(sel_pick_kernel, dim3(1), dim3(256), 0, hs, st, hist, bits[pass],
                            pass == 2 ? 1 : 0, status);
     }
-    const int64_t chunk = cdiv(count, kSelWgs);
+    const int64_t chunk = cdiv(cdiv(count, kSelWgs), 4) * 4;
     hipLaunchKernelGGL(sel_count_kernel, dim3(kSelWgs), dim3(256), 0, hs, V, count, chunk, st, cnt,
                        status);
     hipLaunchKernelGGL(sel_scan_kernel, dim3(1), dim3(256), 0, hs, cnt, k, st, off, adm, nnz_out,

@@ -285,3 +285,21 @@ def test_lambda_max_two_threads(qe):
     for t in threads:
         t.join()
     assert got == [[alone[0]] * 4, [alone[1]] * 4]
+
+
+@pytest.mark.parametrize("count", [1, 3, 5, 1023, 4095, 4097, 5003, 1024 * 1024 + 7])
+def test_topk_chunk_edges(qe, oracle, count):
+    """Counts that end inside a thread's four values and inside a workgroup's
+    chunk, with ties across both, from a base 4 bytes off."""
+    V = synth.gaussian((1, count), seed=count % 1000)
+    V.reshape(-1)[::3] = 0.75
+    V.reshape(-1)[1::7] = -0.75
+    buf = torch.full((count + 9,), float("inf"), device="cuda")
+    Vd = buf[1:1 + count].view(1, count)
+    Vd.copy_(dev(V))
+    for s in sorted({1, (count + 1) // 2, count}):
+        out, sup, nnz = qe.topk_abs(Vd, s)
+        ref_sup, ref_dense = oracle.topk_abs(V, s)
+        n = int(host(nnz)[0])
+        assert n == len(ref_sup) and np.array_equal(host(sup)[:n], ref_sup)
+        assert np.array_equal(host(out), ref_dense)
