@@ -320,7 +320,7 @@ def main():
 
     t_steps = resumed_sweeps(P.QE_CD_DENSE)
     # the same sweeps on the default path: past convergence almost no code
-    # moves, and the block update applies only the few nonzero differences
+    # moves, and the sweeps run row by row, with a rank-1 update per move
     t_converged = resumed_sweeps(0) / sweeps
     # one sweep per call from W = What: events around each of sweeps 2..K
     # (with its objective, carried from call to call as inside the step's

@@ -497,10 +497,10 @@ __global__ __launch_bounds__(256) void power_last_kernel(const double* part, int
 // ---- the same with Sigma kept on the chip (p <= 4096)
 // One launch runs a whole batch of iterations: workgroup b holds rows 8 RW b .. 8 RW b
 // + 8 RW - 1 of Sigma in registers (RW rows per wavefront, 4 NC values of each per
-// lane; RW = 2 above 2048 channels), so that an iteration moves only y.  y travels between the workgroups as 64-bit words
-// of a value and the iteration that made it, stored and polled with agent-scope
-// atomics: the word carries its own flag, so no other ordering is needed.  Two
-// buffers alternate; a workgroup writes iteration k + 1 only after it has read all of
+// lane; RW = 2 above 2048 channels), so that an iteration moves only y.  y travels
+// between the workgroups as 64-bit words of a value and the iteration that made it,
+// stored and polled with agent-scope atomics: the word carries its own flag, so no
+// other ordering is needed.  Two buffers alternate; a workgroup writes iteration k + 1 only after it has read all of
 // k, when every other one has done with k - 1.  The launch is cooperative (all
 // workgroups resident), and a wait that lasts kMaxPolls polls gives up: the batch
 // then reports it and the call falls back to a launch per iteration.
