@@ -161,10 +161,14 @@ qe_status qe_grid_minmax(const float* W, const float* H, int64_t q, int64_t p, i
  * 128): inside a block the rank-1 updates touch only the block's columns;
  * the accumulated block update is then applied to every column as one
  * matrix-core GEMM.  A sweep that starts from valid codes and moves few of them
- * runs row by row instead (p <= 16384, no relaxed sweeps, none of QE_CD_DENSE and
- * QE_CD_FP32; decided on the device from a sample of the state): per move one
- * rank-1 update of the row, nothing for a kept code.  The result equals the
- * column-by-column algorithm up to floating-point rounding in either form.
+ * runs row by row instead (p <= 16384, no QE_RELAX_PERIOD, none of QE_CD_DENSE and
+ * QE_CD_FP32; decided on the device from a sample of the state before the sweep, and
+ * then for the rest of the call; after QE_INIT_FROM_W, whose later sweeps move few,
+ * at the latest with the fifth sweep, the ninth if q p p is at least 1.5e11): per move
+ * one rank-1 update of the row, nothing for a kept code.  The result equals the
+ * column-by-column algorithm up to floating-point rounding in either form; R's
+ * rounding depends on the form, so a call of K sweeps and K resumed calls agree bit
+ * for bit where they make the same choices, and up to rounding otherwise.
  *
  * W:      q x p, device, read (only for R initialisation and the objective).
  * Sigma:  p x p, device, symmetric with Sigma_jj > 0 (else QE_ERR_DIAG).

@@ -174,7 +174,7 @@ qe_status qe_cd_sweep(const float* W, const float* Sigma, int64_t q, int64_t p, 
     hipStream_t s = as_stream(stream);
     if (clear_status(ws, s) != QE_OK) return QE_ERR_HIP;
     return launch_cd(W, Sigma, q, p, bits, scale, zero, W_hat, codes, R, nullptr, sweeps, block,
-                     flags, obj, 1, (flags & QE_OBJ_IN) ? obj : nullptr, 0, ws, s);
+                     flags, obj, 1, (flags & QE_OBJ_IN) ? obj : nullptr, (flags & QE_INIT_FROM_W) ? 0 : -1, ws, s);
 }
 
 qe_status qe_cd_sweep_noalloc(const float* W, const float* Sigma, int64_t q, int64_t p, int bits,
@@ -194,7 +194,7 @@ qe_status qe_cd_sweep_noalloc(const float* W, const float* Sigma, int64_t q, int
     // the previous call's status word is still there
     if (clear_status(ws, s) != QE_OK) return QE_ERR_HIP;
     st = launch_cd(W, Sigma, q, p, bits, scale, zero, W_hat, codes, R, nullptr, sweeps, block,
-                   flags, obj, 1, (flags & QE_OBJ_IN) ? obj : nullptr, 0, ws, s);
+                   flags, obj, 1, (flags & QE_OBJ_IN) ? obj : nullptr, (flags & QE_INIT_FROM_W) ? 0 : -1, ws, s);
     if (st != QE_OK) return st;
     if (status) {
         hipLaunchKernelGGL(status_copy_kernel, dim3(1), dim3(64), 0, s,

@@ -27,6 +27,7 @@
 // This blocked form runs the sweeps that move most coordinates (the first from
 // What = W, relaxed sweeps) and those of QE_CD_DENSE, QE_CD_FP32 and p > 16384;
 // the others run row by row (cd_rows.hip).
+#include <climits>
 #include <utility>
 
 #include "nt_x3.h"
@@ -35,14 +36,14 @@
 namespace qe {
 
 // ---------------------------------------------------------------- setup kernels
-// inv_d = 1 / diag(Sigma), inv_s = 1 / scale, with their checks; `moving` (n ints,
-// or n = 0) starts at 0.
+// inv_d = 1 / diag(Sigma), inv_s = 1 / scale, with their checks; no sweep of the call
+// has been given to the row form yet.
 __global__ void prep_kernel(const float* __restrict__ Sigma, int64_t p, float* inv_d,
                             const float* __restrict__ scale, const float* __restrict__ zero,
-                            int64_t q, float* inv_s, int* moving, int n, int* status)
+                            int64_t q, float* inv_s, RowsChoice* choice, int* status)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n) moving[t] = 0;
+    if (t == 0) *choice = RowsChoice{0, INT_MAX};
     if (t < p) {
         const float d = Sigma[t * p + t];
         if (!(d > 0.f) || !isfinite(d)) {
@@ -157,10 +158,10 @@ __global__ __launch_bounds__(256) void obj_partial_kernel(const float* __restric
 // equal prev).
 __global__ __launch_bounds__(256) void sum_partials_kernel(const double* partial, int n,
                                                            const double* prev, double* out,
-                                                           const int* gate, int limit,
+                                                           const int* first, int sweep,
                                                            const int* status)
 {
-    if (failed(status) || (gate && *gate <= limit)) return;
+    if (failed(status) || (first && *first <= sweep)) return;
     __shared__ double sh[256];
     double acc = 0.0;
     for (int e = threadIdx.x; e < n; e += blockDim.x) acc += partial[e];
@@ -199,8 +200,8 @@ struct StepArgs {
     double* fpart;        // per panel wave: the objective change of this sweep's moves so far
     int fobj;             // accumulate fpart (the per-sweep objective is wanted)
     int ffirst;           // first launch of a sweep: fpart is written, not added to
-    const int* gate;      // optional sweep: runs only while *gate > limit (else null)
-    int limit;
+    const int* first;     // optional sweep: runs only before *first (else null)
+    int sweep;
     const int* status;
 };
 
@@ -975,7 +976,7 @@ constexpr int step_lds_floats()
 template <int SLOTS>
 __global__ __launch_bounds__(256, 2) void cd_step_kernel(StepArgs a)
 {
-    if (failed(a.status) || (a.gate && *a.gate <= a.limit)) return;
+    if (failed(a.status) || (a.first && *a.first <= a.sweep)) return;
     static_assert(step_lds_floats<SLOTS>() >= kLaCols * kLaStride, "look-ahead staging fits");
     __shared__ __attribute__((aligned(16))) float lds[step_lds_floats<SLOTS>()];
     if ((int)blockIdx.x < a.n_panel)
@@ -986,19 +987,22 @@ __global__ __launch_bounds__(256, 2) void cd_step_kernel(StepArgs a)
 
 // ---------------------------------------------------------------- host side
 // A sweep from valid codes runs row by row (cd_rows.hip) when few coordinates
-// move.  That is known on the device only: for the first sweeps of a call both
-// forms are enqueued, and a count over a sample of rows, taken before the
-// sweep, decides which of them does the work.  An unused blocked sweep costs
-// about 2.9 us per empty launch (50 us at 4096 columns), so the choice is not
-// offered for ever: from the fourth sweep after What = W on the row form was the
-// faster one on every layer of up to 4096 x 4096 measured; strongly coupled large
-// ones move 3% of their codes for longer (8192 x 6144, rho = 0.9: the fifth sweep
-// takes 5.2 ms row by row, 3.9 ms blocked), and there the launches weigh less.
-constexpr int kMaxOptional = 8;          // sweeps 0 .. 7 of a call
-constexpr int kFewOptional = 4;
+// move.  That is known on the device only: both forms are enqueued, and a count over a
+// sample of rows, taken before the sweep, decides which of them does the work.  Once
+// it falls to the row form, the rest of the call runs there, in one launch.
+// An unused blocked sweep costs about 2.9 us per empty launch (50 us at 4096
+// columns).  From codes that the caller brings, any sweep may move most of them:
+// every one is sampled (4096 x 4096, rho = 0.9, from rounded weights, 13 to 17% of the
+// codes move for ten sweeps: 26.6 ms with the row form from the fifth sweep on, 11.3
+// so).  From What = W the first sweep leaves few: 10 to 30% move in the second, 1 to
+// 3.5% in the fifth, on every layer, bit width and conditioning tried, and there the
+// row form took at most 1.15 times the blocked sweep (large layers: the line lies
+// lower, and the launches weigh less).  So the choice is offered for its first sweeps.
+constexpr int kFewOptional = 4;          // sweeps 1 .. 3 after What = W
+constexpr int kManyOptional = 8;         // with at least kManyWork
 constexpr double kManyWork = 1.5e11;     // q p^2
-constexpr int kMovingWord = 16;          // their counts, in the status region
-static_assert((kMovingWord + kMaxOptional) * sizeof(int) <= kStatusBytes, "counts fit");
+constexpr int kChoiceWord = 16;          // RowsChoice, in the status region
+static_assert(kChoiceWord * sizeof(int) + sizeof(RowsChoice) <= kStatusBytes, "the choice fits");
 
 static int block_width(int block) { return block == 0 ? 128 : block; }
 
@@ -1064,7 +1068,7 @@ static qe_status launch_steps(StepArgs base, float* d0, float* d1, int* nz0, int
 qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, int bits,
                     const float* scale, const float* zero, float* Wh, uint8_t* codes, float* R,
                     const float* H, int sweeps, int block, uint32_t flags, double* obj,
-                    int obj_stride, const double* f_in, int sweep0, void* ws, hipStream_t s)
+                    int obj_stride, const double* f_in, int since_init, void* ws, hipStream_t s)
 {
     const int B = block_width(block);
     const int S = super_width(B);
@@ -1091,9 +1095,9 @@ qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, in
             if (launch_nonfinite_scan(inputs[k], counts[k], status, s) != QE_OK) return QE_ERR_HIP;
         if (launch_nonfinite_scan(H, q * p, status, s) != QE_OK) return QE_ERR_HIP;
     }
-    int* const moving = status + kMovingWord;
+    RowsChoice* const choice = reinterpret_cast<RowsChoice*>(status + kChoiceWord);
     hipLaunchKernelGGL(prep_kernel, dim3((unsigned)cdiv(std::max(p, q), 256)), dim3(256), 0, s, Sigma, p,
-                       inv_d, scale, zero, q, inv_s, moving, sweep0 == 0 ? kMaxOptional : 0, status);
+                       inv_d, scale, zero, q, inv_s, choice, status);
     const bool vec4 = aligned16(Sigma) && aligned16(W) && aligned16(Wh) && (p % 4 == 0) &&
                       (!H || aligned16(H));
     if (flags & QE_INIT_FROM_W) {
@@ -1140,10 +1144,10 @@ qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, in
     bool prev_relaxed = false;
     const double* const f0 = f_prev;
     const bool rows = !base.dense && !base.fp32 && period == 0 && cd_rows_fits(p);
-    const int limit = rows ? cd_rows_limit(q, p) : -1;
+    const bool warm = since_init < 0;    // from codes that the caller brought
+    const int limit = rows ? cd_rows_limit(q, p, warm) : -1;
     const bool large = (double)q * (double)p * (double)p >= kManyWork;
-    const int max_optional = limit < 0 ? 0 : large ? kMaxOptional : kFewOptional;
-    int opt0 = -1;                       // first sweep from valid codes (with rows)
+    int opt0 = -1, opt1 = -1;            // with rows: sweeps from valid codes, optional ones [opt0, opt1)
     for (int sw = 0; sw < sweeps; ++sw) {
         const int k = sw + 1;
         base.relax = (period > 0 && k % period == 0 && k != sweeps) ? 1 : 0;
@@ -1157,16 +1161,15 @@ qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, in
         base.intd = (base.codes_valid && !base.relax) ? 1 : 0;
         prev_relaxed = base.relax != 0;
         if (rows && base.intd) {
-            if (opt0 < 0) opt0 = sw;
-            if (sweep0 + sw >= max_optional) break;
+            if (opt0 < 0) opt0 = opt1 = sw;
+            if (limit < 0 || (!warm && since_init + sw >= (large ? kManyOptional : kFewOptional))) break;
             // optional: these launches do nothing when few coordinates move
-            int* const cnt = moving + sweep0 + sw;
-            const bool before = sw > opt0 || (sw == 0 && sweep0 > 1);
-            if (launch_cd_sample(R, Wh, inv_d, scale, zero, inv_s, q, p, base.maxq,
-                                 before ? cnt - 1 : nullptr, limit, cnt, status, s) != QE_OK)
+            if (launch_cd_sample(R, Wh, inv_d, scale, zero, inv_s, q, p, base.maxq, sw, limit, choice, status,
+                                 s) != QE_OK)
                 return QE_ERR_HIP;
-            base.gate = cnt;
-            base.limit = limit;
+            base.first = &choice->first;
+            base.sweep = sw;
+            opt1 = sw + 1;
         }
         qe_status st;
         switch (B) {
@@ -1179,17 +1182,15 @@ qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, in
         if (obj) {
             double* out = obj + (size_t)sw * obj_stride;
             hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, s, fpart, n_fpart,
-                               f_prev, out, base.gate, base.limit, status);
+                               f_prev, out, base.first, base.sweep, status);
             if (hipGetLastError() != hipSuccess) return QE_ERR_HIP;
             f_prev = out;
         }
     }
-    if (opt0 >= 0) {
-        const int opt1 = std::max(opt0, std::min(sweeps, max_optional - sweep0));
+    if (opt0 >= 0)
         return launch_cd_rows(Sigma, q, p, inv_d, scale, zero, inv_s, base.maxq, Wh, codes, R, sweeps,
-                              moving + sweep0 + opt0, opt0, opt1, limit, obj, obj_stride, f0,
+                              &choice->first, opt0, opt1, obj, obj_stride, f0,
                               reinterpret_cast<double*>(d0), q * S / 2, status, s);
-    }
     return QE_OK;
 }
 

@@ -49,20 +49,14 @@ struct RowsArgs {
     int64_t q, p;
     float maxq;
     int k0, k1;           // sweeps of the call that this launch may run
-    const int* moving;    // sampled counts of sweeps opt0 .. opt1 - 1 (see cd_sample_kernel)
-    int opt0, opt1, limit;
+    const int* first;     // the optional sweep that was given to this form (see cd_sample_kernel)
+    int opt1;             // the first sweep that is not optional
     double* fpart;        // (k1 - k0) x q: objective change of each row and sweep (or null)
     const int* status;
 };
 
-// The first sweep that runs here: the first optional one whose sample holds at
-// most `limit` moves, else the first that is not optional.
-__device__ __forceinline__ int first_sweep(const int* moving, int opt0, int opt1, int limit)
-{
-    int k = opt0;
-    while (k < opt1 && moving[k - opt0] > limit) ++k;
-    return k;
-}
+// The first sweep of a launch that runs here.
+__device__ __forceinline__ int first_sweep(const RowsArgs& a) { return max(a.k0, min(*a.first, a.opt1)); }
 
 // Four consecutive floats; those at or past the end of the row read as 0.
 template <bool FULL>
@@ -173,7 +167,7 @@ template <int G, bool MULTI>
 __global__ __launch_bounds__(MULTI ? 1024 : 64) void cd_rows_kernel(RowsArgs a)
 {
     if (failed(a.status)) return;
-    const int start = max(a.k0, first_sweep(a.moving, a.opt0, a.opt1, a.limit));
+    const int start = first_sweep(a);
     if (start >= a.k1) return;
     __shared__ int2 list[2][MULTI ? 256 * G : 1];
     __shared__ int count[2];
@@ -286,7 +280,7 @@ __global__ __launch_bounds__(256) void rows_sum_kernel(RowsArgs a)
 {
     if (failed(a.status)) return;
     const int k = a.k0 + blockIdx.x;
-    if (k < max(a.k0, first_sweep(a.moving, a.opt0, a.opt1, a.limit))) return;
+    if (k < first_sweep(a)) return;
     __shared__ double sh[256];
     double* part = a.fpart + (int64_t)blockIdx.x * a.q;
     double acc = 0.0;
@@ -299,7 +293,7 @@ __global__ __launch_bounds__(256) void rows_sum_kernel(RowsArgs a)
 __global__ void rows_objective_kernel(RowsArgs a, const double* f0, double* obj, int stride)
 {
     if (failed(a.status) || threadIdx.x != 0) return;
-    const int start = max(a.k0, first_sweep(a.moving, a.opt0, a.opt1, a.limit));
+    const int start = first_sweep(a);
     if (start >= a.k1) return;
     double f = start > 0 ? obj[(int64_t)(start - 1) * stride] : (f0 ? *f0 : 0.0);
     for (int k = start; k < a.k1; ++k) {
@@ -308,21 +302,22 @@ __global__ void rows_objective_kernel(RowsArgs a, const double* f0, double* obj,
     }
 }
 
-// How many coordinates of a sample of rows (every q / gridDim.x-th) would move
-// from the present state, into *moving (zeroed before).  `prev` (or null): the
-// count of the sweep before; once a sweep has run row by row, so do the later
-// ones, and theirs stays 0.
+// Whether sweep k runs row by row: no more than `limit` coordinates of a sample of
+// rows (every q / gridDim.x-th) would move from the present state.  The last workgroup
+// to count decides, sets choice->first and leaves the count at 0 (one 64-bit atomic
+// carries both sums, so nothing has to be ordered).  Once a sweep has been given to the
+// row form, so are the later ones of the call.
 __global__ __launch_bounds__(256) void cd_sample_kernel(const float* __restrict__ R,
                                                         const float* __restrict__ Wh,
                                                         const float* __restrict__ inv_d,
                                                         const float* __restrict__ scale,
                                                         const float* __restrict__ zero,
                                                         const float* __restrict__ inv_s, int64_t q,
-                                                        int64_t p, float maxq, const int* prev, int limit,
-                                                        int* moving, const int* status)
+                                                        int64_t p, float maxq, int k, int limit,
+                                                        RowsChoice* choice, const int* status)
 {
-    if (failed(status)) return;
-    if (prev && *prev <= limit) return;
+    if (failed(status) || choice->first < k) return;
+    __shared__ int sh[4];
     const int64_t i = (int64_t)blockIdx.x * q / gridDim.x;
     const float z = zero[i], is = inv_s[i];
     int n = 0;
@@ -335,10 +330,19 @@ __global__ __launch_bounds__(256) void cd_sample_kernel(const float* __restrict_
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
-    if ((threadIdx.x & 63) == 0 && n) atomicAdd(moving, n);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = n;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    constexpr unsigned long long kOne = 1ull << 40;
+    const unsigned long long add = kOne + (unsigned)(sh[0] + sh[1] + sh[2] + sh[3]);
+    const unsigned long long all = atomicAdd(&choice->count, add) + add;
+    if (all < kOne * gridDim.x) return;
+    if ((long long)(all % kOne) <= limit) choice->first = k;
+    choice->count = 0;
 }
 
 constexpr int64_t kRowsMaxP = 16384;     // 16 waves of 1024 columns
+constexpr int64_t kOneWave = 1024;       // up to here one wave holds a row
 constexpr int kSampleRows = 256;
 
 bool cd_rows_fits(int64_t p) { return p <= kRowsMaxP; }
@@ -350,48 +354,61 @@ bool cd_rows_fits(int64_t p) { return p <= kRowsMaxP; }
 // or the column steps of its launches, 50 us for 256 columns, where rows are few.
 // The line lies where the two are equal: 3.3% at 4096 x 4096 (measured: 5.1%,
 // 1.60 against 1.13 ms; 0.9%, 0.38 against 1.06 ms), 2.6% at 4096 x 11008 (3.5%,
-// 9.9 against 6.9 ms; 0.7%, 2.3 against 6.6 ms).  Above 12% no layer of so few
-// rows is worth the blocked launches (1003 x 3001, 5%: 0.36 against 0.91 ms).
+// 9.9 against 6.9 ms; 0.7%, 2.3 against 6.6 ms).
 // Strongly coupled channels move less than the sample says (the first move
 // settles its neighbours): the blocked form is then kept a few sweeps longer.
-
-int cd_rows_limit(int64_t q, int64_t p)
+//
+// Above 12%, where rows are few, the bytes do not bound a move any more but the
+// search's chain does: 20 us and 0.45 us per move for one wave (128 x 300, 56%: 0.11
+// against 0.08 ms; 16 x 1024, 59%: 0.27 against 0.15), 0.87 us for several (16 x 4096,
+// 62%: 2.24 against 0.56 ms; 64 x 12000, 74%: 7.5 against 1.8), and 38 us for 256
+// columns of the blocked form.  Only codes that the caller brings (warm) move so many:
+// after What = W such a layer is always taken row by row (the launches would cost more
+// than they save: 1003 x 3001, 5%: 0.36 against 0.50 ms), and so is a layer of less
+// than one panel, 16 rows (8 x 4096 from rounded weights: 17% move, 0.84 against 0.55
+// ms, and ten sweeps 6.9 against 6.0 ms).
+int cd_rows_limit(int64_t q, int64_t p, bool warm)
 {
     const double work = (double)q * (double)p * (double)p;
     const double bw = 4.0 * (double)p * (double)p <= 2.0e8 ? 9.0e12 : 7.0e12;
     const double dense = std::max(2.0 * work / 135.0e12, (double)(cdiv(p, 256) + 1) * 50.0e-6);
-    const double f = dense * bw / (4.0 * work);
-    if (f > 0.12) return -1;
+    double f = dense * bw / (4.0 * work);
+    if (f > 0.12) {
+        if (!warm || q < 16) return -1;
+        const double move = p <= kOneWave ? 0.45e-6 : 0.87e-6;
+        f = std::min(f, ((double)cdiv(p, 256) * 38.0e-6 - 20.0e-6) / ((double)p * move));
+        if (f >= 1.0) return -1;
+    }
     return (int)(f * (double)std::min<int64_t>(q, kSampleRows) * (double)p);
 }
 
 qe_status launch_cd_sample(const float* R, const float* Wh, const float* inv_d, const float* scale,
                            const float* zero, const float* inv_s, int64_t q, int64_t p, float maxq,
-                           const int* prev, int limit, int* moving, const int* status, hipStream_t s)
+                           int k, int limit, RowsChoice* choice, const int* status, hipStream_t s)
 {
     hipLaunchKernelGGL(cd_sample_kernel, dim3((unsigned)std::min<int64_t>(q, kSampleRows)), dim3(256), 0,
-                       s, R, Wh, inv_d, scale, zero, inv_s, q, p, maxq, prev, limit, moving, status);
+                       s, R, Wh, inv_d, scale, zero, inv_s, q, p, maxq, k, limit, choice, status);
     return hipGetLastError() == hipSuccess ? QE_OK : QE_ERR_HIP;
 }
 
-// Sweeps [opt0, sweeps) of a call, of which [opt0, opt1) are optional.  fpart:
-// room for fpart_count doubles (at least one sweep of q).
+// Sweeps [opt0, sweeps) of a call, of which [opt0, opt1) are optional (those before
+// *first have run in the blocked form).  fpart: room for fpart_count doubles (at least
+// one sweep of q).
 qe_status launch_cd_rows(const float* Sigma, int64_t q, int64_t p, const float* inv_d, const float* scale,
                          const float* zero, const float* inv_s, float maxq, float* Wh, uint8_t* codes,
-                         float* R, int sweeps, const int* moving, int opt0, int opt1, int limit, double* obj,
-                         int obj_stride, const double* f0, double* fpart, int64_t fpart_count,
-                         const int* status, hipStream_t s)
+                         float* R, int sweeps, const int* first, int opt0, int opt1, double* obj, int obj_stride,
+                         const double* f0, double* fpart, int64_t fpart_count, const int* status, hipStream_t s)
 {
     const int per = obj ? (int)std::max<int64_t>(1, std::min<int64_t>(sweeps, fpart_count / q)) : sweeps;
     for (int k = opt0; k < sweeps; k += per) {
         RowsArgs a{Sigma, inv_d, scale, zero, inv_s, Wh, codes, R, q, p, maxq, k, std::min(k + per, sweeps),
-                   moving, opt0, opt1, limit, obj ? fpart : nullptr, status};
+                   first, opt1, obj ? fpart : nullptr, status};
         const dim3 grid((unsigned)q);
 #define QE_ROWS(G, M) \
     hipLaunchKernelGGL((cd_rows_kernel<G, M>), grid, dim3((unsigned)(64 * cdiv(p, 256 * G))), 0, s, a)
         if (p <= 256) QE_ROWS(1, false);
         else if (p <= 512) QE_ROWS(2, false);
-        else if (p <= 1024) QE_ROWS(4, false);
+        else if (p <= kOneWave) QE_ROWS(4, false);
         else QE_ROWS(4, true);
 #undef QE_ROWS
         if (obj)

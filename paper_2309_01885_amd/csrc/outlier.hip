@@ -885,7 +885,8 @@ qe_status launch_outlier(const float* W, const float* Sigma, int64_t q, int64_t 
         // the CD sweep's objective builds on g after the previous IHT step
         qe_status st = launch_cd(W, Sigma, q, p, bits, scale, zero, Wh, codes, E, H, 1, block, f,
                                  obj ? obj + 2 * it : nullptr, 2,
-                                 obj && it > 0 ? obj + 2 * it - 1 : nullptr, it, ws, hs);
+                                 obj && it > 0 ? obj + 2 * it - 1 : nullptr,
+                                 (flags & QE_INIT_FROM_W) ? it : -1, ws, hs);
         if (st != QE_OK) return st;
         if (s > 0) {
             const int nxt = cur ^ 1;

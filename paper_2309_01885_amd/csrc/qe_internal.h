@@ -457,20 +457,24 @@ size_t objective_ws_bytes(int64_t q, int64_t p);
 qe_status launch_objective(const float* W, const float* Wh, const float* H, const float* Sigma,
                            int64_t q, int64_t p, double* out, void* ws, hipStream_t s);
 size_t cd_ws_bytes(int64_t q, int64_t p, int block);
+// since_init: sweeps since What = W (0 for a call that starts there), or -1 from What
+// and codes that the caller brought.
 qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, int bits,
                     const float* scale, const float* zero, float* Wh, uint8_t* codes, float* R,
                     const float* H, int sweeps, int block, uint32_t flags, double* obj,
-                    int obj_stride, const double* f_in, int sweep0, void* ws, hipStream_t s);
+                    int obj_stride, const double* f_in, int since_init, void* ws, hipStream_t s);
+// Which sweeps of a call run row by row: the sample being counted (workgroups that have
+// counted, from bit 40 on, and their moves) and the first sweep that does (device memory).
+struct RowsChoice { unsigned long long count; int first; };
 bool cd_rows_fits(int64_t p);
-int cd_rows_limit(int64_t q, int64_t p);
+int cd_rows_limit(int64_t q, int64_t p, bool warm);
 qe_status launch_cd_sample(const float* R, const float* Wh, const float* inv_d, const float* scale,
                            const float* zero, const float* inv_s, int64_t q, int64_t p, float maxq,
-                           const int* prev, int limit, int* moving, const int* status, hipStream_t s);
+                           int k, int limit, RowsChoice* choice, const int* status, hipStream_t s);
 qe_status launch_cd_rows(const float* Sigma, int64_t q, int64_t p, const float* inv_d, const float* scale,
                          const float* zero, const float* inv_s, float maxq, float* Wh, uint8_t* codes,
-                         float* R, int sweeps, const int* moving, int opt0, int opt1, int limit, double* obj,
-                         int obj_stride, const double* f0, double* fpart, int64_t fpart_count,
-                         const int* status, hipStream_t s);
+                         float* R, int sweeps, const int* first, int opt0, int opt1, double* obj, int obj_stride,
+                         const double* f0, double* fpart, int64_t fpart_count, const int* status, hipStream_t s);
 qe_status launch_residual_dot(const float* W, const float* Wh, const float* H, const float* R,
                               int64_t count, double* out, double* part, const int* status,
                               hipStream_t s);

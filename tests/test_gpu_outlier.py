@@ -203,6 +203,41 @@ def test_structured_outlier_matches_oracle(qe, oracle, q, p, ncols, corr):
     assert np.mean(host(codes).astype(np.int32) != ref.codes) <= 1e-3
 
 
+def test_iterations_choose_their_form_anew(qe):
+    """An IHT step moves E, so a sweep of few moves may be followed by one of many (here
+    through a step far too long): every iteration of a call decides by its own state,
+    and a call of four iterations equals four calls of one, bit for bit."""
+    q = p = 2048
+    W = synth.gaussian((q, p), seed=45, std=0.02)
+    a = np.arange(p)
+    S = dev((0.5 ** np.abs(a[:, None] - a[None, :])).astype(np.float32))
+    s = q * p // 10
+    H0, sup0, n0 = qe.topk_abs(dev(W), s)
+    Wd = dev(W)
+    scale, zero = qe.grid_minmax(Wd, 4, H=H0)
+
+    def run(calls):
+        H, sup, nnz = H0.clone(), sup0.clone(), n0.clone()
+        Wh, E = torch.empty_like(Wd), torch.empty_like(Wd)
+        codes = torch.zeros((q, p), dtype=torch.uint8, device="cuda")
+        moved = []
+
+        def sweep(lam, sweeps, flags):
+            before = codes.clone()
+            qe.cd_outlier_sweep(Wd, S, 4, scale, zero, Wh, codes, H, E, s, lam, sup, nnz, sweeps,
+                                flags=flags)
+            moved.append(float((codes != before).float().mean()))
+        sweep(3.1, 3, qe.QE_INIT_FROM_W)
+        for k in calls:
+            sweep(0.1, k, qe.QE_R_VALID | qe.QE_CODES_VALID)
+        return moved[1:], [host(t) for t in (codes, Wh, H, E, sup, nnz)]
+    moved, each = run([1] * 4)
+    print("moved", moved)
+    assert moved[1] < 0.06 and moved[2] > 0.2        # the line lies at 0.118 of a static count
+    for x, y in zip(each, run([4])[1]):
+        assert np.array_equal(x, y)
+
+
 def test_outlier_debug_checks_scan_h(qe, oracle):
     """QE_DEBUG_CHECKS in the outlier-aware call also scans H."""
     q, p, bits = 48, 96, 3

@@ -59,6 +59,35 @@ def test_choice_on_the_device(qe, oracle):
                    cut(g["whats"]), cut(g["Rs"]), label="choice 2048x2048")
 
 
+def ar1(p, rho):
+    """Sigma of AR(1) channels, exactly symmetric, with 1% damping."""
+    a = np.arange(p)
+    return (rho ** np.abs(a[:, None] - a[None, :]) + 0.01 * np.eye(p)).astype(np.float32)
+
+
+@pytest.mark.parametrize("q,p", [(512, 512), (70, 1501), (2048, 2048)])
+def test_warm_start_that_keeps_moving(qe, oracle, q, p):
+    """From codes far off, most coordinates move in every one of seven sweeps (above
+    the line of any shape): all of them run in the blocked form, also those past the
+    first few of a call and in layers that What = W always leaves to the row form.
+    (QE_RELAX_PERIOD keeps a call in the blocked form, here without a relaxed sweep.)"""
+    W, S32 = synth.gaussian((q, p), seed=55, std=0.02), ar1(p, 0.9)
+    scale, zero = oracle.grid_minmax(W, 4)
+    c0 = synth.integers((q, p), seed=56, lo=0, hi=16)
+    W0 = oracle.dequant(c0, scale, zero).astype(np.float32)
+    start = dict(W0=W0, codes0=c0)
+    want = gpu_cd(qe, W, S32, 4, scale, zero, 7, extra=qe.QE_RELAX_PERIOD(255), **start)
+    moved = [np.mean(a != b) for a, b in zip([c0] + want["hist"], want["hist"])]
+    assert min(moved) > 0.3, moved
+    g = gpu_cd(qe, W, S32, 4, scale, zero, 7, **start)
+    one = gpu_cd(qe, W, S32, 4, scale, zero, 7, per_sweep=False, **start)
+    for k in range(7):
+        assert np.array_equal(g["Rs"][k], want["Rs"][k]), f"sweep {k + 1}"
+    for k in ("What", "codes", "R"):
+        assert np.array_equal(one[k], want[k])
+    assert one["obj"] == g["obj"] == want["obj"]
+
+
 def test_fixed_point_and_no_objective(qe, oracle):
     """Rows that stop moving leave the later sweeps early: the objective stays,
     and a call without one gives the same state."""
