@@ -477,28 +477,32 @@ __device__ inline float absmax4(float m, f32x4 v)
     return fmaxf(m, fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))));
 }
 
-// Channel-major X (p x n): one workgroup per channel.
+// Channel-major X (p x n): workgroup (channel, slice y of the tokens).  One slice
+// writes the channel's exponent, several their largest |x| to part[y * p + channel];
+// chan_exp_np_kernel reduces those.  Rows need no alignment beyond their four bytes.
 __global__ __launch_bounds__(256) void chan_exp_pn_kernel(const float* __restrict__ X, int64_t n,
-                                                          int x_vec4, int* __restrict__ chexp,
-                                                          const int* status)
+                                                          int64_t slice, int* __restrict__ chexp,
+                                                          float* __restrict__ part, const int* status)
 {
     if (failed(status)) return;
     __shared__ float sh[4];
-    const float* row = X + (int64_t)blockIdx.x * n;
+    const int64_t t0 = blockIdx.y * slice, len = min(slice, n - t0);
+    const float* row = X + (int64_t)blockIdx.x * n + t0;
     float m = 0.f;
-    if (x_vec4) {
-        // n % 4 == 0 and 16-byte aligned rows
-        const f32x4* r4 = reinterpret_cast<const f32x4*>(row);
 #pragma unroll 4
-        for (int64_t i = threadIdx.x; i < n / 4; i += 256) m = absmax4(m, r4[i]);
-    } else {
-        for (int64_t i = threadIdx.x; i < n; i += 256) m = fmaxf(m, fabsf(row[i]));
-    }
+    for (int64_t i = threadIdx.x; i < len / 4; i += 256)
+        m = absmax4(m, *reinterpret_cast<const f32x4a4*>(row + 4 * i));
+    if (threadIdx.x < len % 4) m = fmaxf(m, fabsf(row[len / 4 * 4 + threadIdx.x]));
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
     __syncthreads();
-    if (threadIdx.x == 0) chexp[blockIdx.x] = chan_exp(fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3])));
+    if (threadIdx.x != 0) return;
+    m = fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
+    if (gridDim.y == 1)
+        chexp[blockIdx.x] = chan_exp(m);
+    else
+        part[blockIdx.y * gridDim.x + blockIdx.x] = m;
 }
 
 // Token-major X (n x p): workgroup (column block of 256, token slice y), lane l of
@@ -568,6 +572,14 @@ static int64_t chan_slices(int64_t p, int64_t n)
     const int64_t few = std::min(cdiv(n, 64), cdiv(256, blocks));
     return std::max<int64_t>(
         1, std::min<int64_t>(std::min<int64_t>(512, 2048 / blocks), std::max(cdiv(n, 256), few)));
+}
+
+// Token slices of chan_exp_pn_kernel: one workgroup per channel where channels fill the
+// chip, else about 1024 of them, at least 16384 tokens a slice (no more slices than
+// chan_slices gives, whose partials they share).
+static int64_t chan_slices_pn(int64_t p, int64_t n)
+{
+    return p >= 512 ? 1 : std::max<int64_t>(1, std::min<int64_t>(cdiv(1024, p), n / 16384));
 }
 
 // Workspace of the channel exponents: p ints and the token-major partials (room for
@@ -739,8 +751,13 @@ static qe_status launch_gram_one(const float* X, int64_t p, int64_t n, int layou
                     hipLaunchKernelGGL(chan_exp_np_kernel, dim3((unsigned)cdiv(p, 64)), dim3(256),
                                        0, s, chpart, p, (int)sl, chexp, status);
                 } else {
-                    hipLaunchKernelGGL(chan_exp_pn_kernel, dim3((unsigned)p), dim3(256), 0, s, X, n,
-                                       x_vec4, chexp, status);
+                    const int64_t slice = cdiv(cdiv(n, chan_slices_pn(p, n)), 4) * 4;
+                    const int64_t sl = cdiv(n, slice);
+                    hipLaunchKernelGGL(chan_exp_pn_kernel, dim3((unsigned)p, (unsigned)sl), dim3(256), 0, s,
+                                       X, n, slice, chexp, chpart, status);
+                    if (sl > 1)
+                        hipLaunchKernelGGL(chan_exp_np_kernel, dim3((unsigned)cdiv(p, 64)), dim3(256),
+                                           0, s, chpart, p, (int)sl, chexp, status);
                 }
                 if (hipGetLastError() != hipSuccess) return QE_ERR_HIP;
             }
