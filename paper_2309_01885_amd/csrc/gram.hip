@@ -628,6 +628,12 @@ static int64_t gram_splits(int64_t p, int64_t n, bool wide)
             best = sp;
             best_cost = cost;
         }
+        // no count from here on costs less than rounds and partials that waste nothing
+        // (long token ranges of few channels have thousands of counts)
+        if ((double)items / (double)slots * ((double)n + kGramWgCostTokens * (double)used) +
+                kGramFinalizeTokensPerTile * (double)(used * tiles) >
+            best_cost)
+            break;
     }
     return best;
 }
