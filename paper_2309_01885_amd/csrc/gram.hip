@@ -600,20 +600,20 @@ static size_t chan_ws_bytes(int64_t p, int64_t n)
 // ceil(n / splits) tokens takes ceil(items / slots) rounds.  The count chosen
 // minimises, in units of one workgroup's time per token, rounds x (tokens per
 // split + a fixed cost per workgroup) + the finalize's reads of the partials,
-// over the counts whose splits hold at most kSplitTokensMax tokens and whose
+// over the counts whose splits hold at most tokens_max tokens and whose
 // partials fit kSplitBudget; ties keep the fewer splits.
 constexpr int64_t kGramSlotsWide = 256, kGramSlotsNarrow = 512;
 constexpr double kGramWgCostTokens = 32.0;        // prologue, pipeline fill, partial-tile store
 constexpr double kGramFinalizeTokensPerTile = 0.11;   // one 64 KB partial tile read in finalize
 
-static int64_t gram_splits(int64_t p, int64_t n, bool wide)
+static int64_t gram_splits(int64_t p, int64_t n, bool wide, int64_t tokens_max)
 {
     const int64_t nt = cdiv(p, kTile);
     const int64_t tiles = nt * (nt + 1) / 2;
     const int64_t ntw = cdiv(p, kWide);
     const int64_t items = wide ? ntw * (ntw + 1) / 2 : tiles;
     const int64_t slots = wide ? kGramSlotsWide : kGramSlotsNarrow;
-    const int64_t s_min = cdiv(n, kSplitTokensMax);
+    const int64_t s_min = cdiv(n, tokens_max);
     const int64_t s_max = std::min<int64_t>(
         (int64_t)(kSplitBudget / ((size_t)tiles * kTileFloats * sizeof(float))), cdiv(n, kKC));
     if (s_min > s_max) return 0;
@@ -638,35 +638,66 @@ static int64_t gram_splits(int64_t p, int64_t n, bool wide)
     return best;
 }
 
-// The fp16 split on the 256 x 256 tiles takes every shape of enough work, whatever
-// p's remainder, the token count's and the rows' alignment: 4544 channels x 16383
-// tokens, token-major, 3.82 ms on the guarded 128 x 128 tiles of the bf16 split,
-// 1.31 ms here.  Below about 3e9 products (and p no multiple of 256) the pass for
-// the channel scales and the padding cost more than they give (995 x 826,
-// token-major: 38 us on the 128 x 128 tiles, 49 us here; 1100 x 5200: 116 and 75 us).
-static bool f2_applies(int64_t p, int64_t n, int layout)
+// Token-major X with a token count that is not a multiple of 32 is taken as
+// an aligned part on the 256 x 256 tiles and a short tail (launch_gram), where
+// those tiles need aligned token ranges.
+constexpr int64_t kTokAlign = 2 * kX3KC;
+
+// Which calls take the fp16 split on the 256 x 256 tiles.  Shapes of whole tiles and
+// stages always do.  The others do from the amount of work on (p^2 n) from which the pass
+// for the channel scales and the padding to 256 channels cost less than the
+// 128 x 128 tiles of the bf16 split lose (times in us, 128 x 128 tiles and here):
+//  - those tiles' guarded loop, the most of them: from 3e9 on (1100 x 2049 token-major
+//    49 and 48, 700 x 8193 68 and 58, 4544 x 16384 3880 and 1320; below, 995 x 2049
+//    44 and 50, 896 x 993 33 and 42);
+//  - their unguarded loop (p a multiple of 128, whole stages, aligned rows), twice as
+//    fast: from 1e10 on (896 x 8192 55 and 56, 1152 x 8192 78 and 70, 640 x 16384 57
+//    and 61), and never at p = 384, where both do the same number of products and the
+//    scale pass comes on top (384 x 180000 198 and 241).
+constexpr double kF2Guarded = 3e9, kF2Unguarded = 1e10;
+
+static bool gram_f2(int64_t p, int64_t n, int layout, bool x_vec4)
 {
     // (the token-major loader's buffer offsets are 32-bit)
-    return (layout & (QE_GRAM_FP32 | QE_GRAM_BF16X3)) == 0 && p <= (int64_t(1) << 24) &&
-           (p % kWide == 0 || (p > kTile && (double)p * (double)p * (double)n >= 3e9));
+    if ((layout & (QE_GRAM_FP32 | QE_GRAM_BF16X3)) != 0 || p > (int64_t(1) << 24)) return false;
+    const bool stages = x_vec4 && n % kTokAlign == 0;
+    // (token-major rows of whole tiles: only the last stage is short)
+    if (p % kWide == 0 && (stages || (layout == QE_LAYOUT_NP && x_vec4 && n > kTokAlign))) return true;
+    const double work = (double)p * (double)p * (double)n;
+    if (p % kTile == 0 && p % kWide != 0 && stages) return p > 3 * kTile && work >= kF2Unguarded;
+    return p > kTile && work >= kF2Guarded;
 }
 
-static bool wide_splits(int64_t p, int64_t n, int layout) { return p % kWide == 0 || f2_applies(p, n, layout); }
+// Token splits of a call.  Work that would do for the fp16 split but runs on the bf16
+// split's unguarded tiles keeps its running sums as short as they would be there: the
+// six products of the bf16 split round twice as often, 384 x 180000 is 1.1e-6 off
+// (Frobenius) with 2144 tokens in a sum, 3.4e-7 with 704 and 6% more time.
+constexpr int64_t kShortSum = 1024;
+
+static int64_t gram_call_splits(int64_t p, int64_t n, int layout, bool f2)
+{
+    if (!f2 && (layout & (QE_GRAM_FP32 | QE_GRAM_BF16X3)) == 0 && p % kWide != 0 && p > kTile &&
+        (double)p * (double)p * (double)n >= kF2Guarded) {
+        const int64_t splits = gram_splits(p, n, false, kShortSum);
+        if (splits != 0) return splits;          // (0: their partials would not fit)
+    }
+    return gram_splits(p, n, f2 || p % kWide == 0, kSplitTokensMax);
+}
 
 static size_t gram_ws_one(int64_t p, int64_t n)
 {
     const int64_t nt = cdiv(p, kTile);
     const int64_t tiles = nt * (nt + 1) / 2;
-    const int64_t splits =
-        std::max(gram_splits(p, n, wide_splits(p, n, 0)), gram_splits(p, n, wide_splits(p, n, QE_GRAM_FP32)));
+    // whatever the layout, the flags and X's alignment choose
+    int64_t splits = 0;
+    for (bool aligned : {false, true}) {
+        const bool f2 = gram_f2(p, n, QE_LAYOUT_PN, aligned);
+        splits = std::max(splits, gram_call_splits(p, n, QE_LAYOUT_PN, f2));
+    }
+    splits = std::max(splits, gram_call_splits(p, n, QE_GRAM_BF16X3, false));
     return kStatusBytes + align256((size_t)splits * tiles * kTileFloats * sizeof(float)) +
            chan_ws_bytes(p, n);
 }
-
-// Token-major X with a token count that is not a multiple of 32 is taken as
-// an aligned part on the 256 x 256 tiles and a short tail (launch_gram), where
-// those tiles need aligned token ranges.
-constexpr int64_t kTokAlign = 2 * kX3KC;
 
 size_t gram_ws_bytes(int64_t p, int64_t n)
 {
@@ -676,6 +707,12 @@ size_t gram_ws_bytes(int64_t p, int64_t n)
     return b;
 }
 
+// 16-byte loads need an aligned base and a row stride that keeps them aligned.
+static bool x_vec4(const float* X, int64_t p, int64_t n, bool trans)
+{
+    return aligned16(X) && (trans ? p : n) % 4 == 0;
+}
+
 static qe_status launch_gram_one(const float* X, int64_t p, int64_t n, int layout, float* Sigma,
                                  int accumulate, float damp, void* ws, hipStream_t s);
 
@@ -683,8 +720,8 @@ qe_status launch_gram(const float* X, int64_t p, int64_t n, int layout, float* S
                       int accumulate, float damp, void* ws, hipStream_t s)
 {
     const bool trans = (layout & ~(QE_GRAM_FP32 | QE_GRAM_BF16X3)) == QE_LAYOUT_NP;
-    const bool whole = f2_applies(p, n, layout) &&
-                       (gram_splits(p, n, true) != 0 || n <= kSplitTokensMax);
+    const bool whole = gram_f2(p, n, layout, x_vec4(X, p, n, trans)) &&
+                       (n <= kSplitTokensMax || gram_call_splits(p, n, layout, true) != 0);
     if (trans && !(layout & QE_GRAM_FP32) && !whole && p % kWide == 0 && n > kTokAlign &&
         n % kTokAlign != 0) {
         // token rows are contiguous: the tail is X's last n % 32 token rows
@@ -702,12 +739,11 @@ static qe_status launch_gram_one(const float* X, int64_t p, int64_t n, int layou
     int* status = static_cast<int*>(ws);
     const int64_t nt = cdiv(p, kTile);
     const int64_t tiles = nt * (nt + 1) / 2;
-    const int64_t splits = gram_splits(p, n, wide_splits(p, n, layout));
     const bool fp32 = (layout & QE_GRAM_FP32) != 0;
-    const bool f2 = f2_applies(p, n, layout);
     const bool trans = (layout & ~(QE_GRAM_FP32 | QE_GRAM_BF16X3)) == QE_LAYOUT_NP;
-    // 16-byte loads need an aligned base and a row stride that keeps them aligned
-    const int x_vec4 = aligned16(X) && ((trans ? p : n) % 4 == 0);
+    const bool vec4 = x_vec4(X, p, n, trans);
+    const bool f2 = gram_f2(p, n, layout, vec4);
+    const int64_t splits = gram_call_splits(p, n, layout, f2);
     // split length: a multiple of the K chunk, at most kSplitTokensMax
     const int64_t split_len = splits == 0 ? n : cdiv(cdiv(n, splits), kKC) * kKC;
     const int64_t used = splits == 0 ? 1 : cdiv(n, split_len);
@@ -723,22 +759,22 @@ static qe_status launch_gram_one(const float* X, int64_t p, int64_t n, int layou
         if (splits == 0) {
             if (trans)
                 hipLaunchKernelGGL((gram_kernel<true, true>), grid, dim3(256), 0, s, X, p, n, nt,
-                                   n, Sigma, accumulate, x_vec4, status);
+                                   n, Sigma, accumulate, vec4 ? 1 : 0, status);
             else
                 hipLaunchKernelGGL((gram_kernel<false, true>), grid, dim3(256), 0, s, X, p, n, nt,
-                                   n, Sigma, accumulate, x_vec4, status);
+                                   n, Sigma, accumulate, vec4 ? 1 : 0, status);
         } else {
             if (trans)
                 hipLaunchKernelGGL((gram_kernel<true, false>), grid, dim3(256), 0, s, X, p, n, nt,
-                                   split_len, parts, accumulate, x_vec4, status);
+                                   split_len, parts, accumulate, vec4 ? 1 : 0, status);
             else
                 hipLaunchKernelGGL((gram_kernel<false, false>), grid, dim3(256), 0, s, X, p, n,
-                                   nt, split_len, parts, accumulate, x_vec4, status);
+                                   nt, split_len, parts, accumulate, vec4 ? 1 : 0, status);
         }
     } else {
         const unsigned grid = (unsigned)(8 * cdiv(tiles * used, 8));
         // every panel inside X, every K range a multiple of 32 (split_len is)
-        const bool full = x_vec4 && p % kTile == 0 && n % (2 * kX3KC) == 0;
+        const bool full = vec4 && p % kTile == 0 && n % (2 * kX3KC) == 0;
 #define QE_GRAM_X3(T, L, F)                                                                     \
     hipLaunchKernelGGL((gram_x3_kernel<T, L, F>), dim3(grid), dim3(256), 0, s, X, p, n, nt, tiles, \
                        used, split_len, dst, accumulate, status)

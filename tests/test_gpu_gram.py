@@ -226,13 +226,13 @@ def test_gram_direct_mode_large_p(qe, oracle, layout, n, mode):
 @pytest.mark.parametrize("layout", [0, 1])
 @pytest.mark.parametrize("offset", [0, 1])
 @pytest.mark.parametrize("p,n", [(129, 181001), (255, 46145), (700, 6127), (1025, 2871), (2300, 569),
-                                 (4097, 179), (256, 33), (512, 1), (768, 15), (257, 15), (385, 31)])
+                                 (4097, 179), (768, 5103), (256, 33), (512, 1), (768, 15), (257, 15), (385, 31)])
 def test_gram_ragged_wide_tiles(qe, oracle, p, n, layout, offset):
     """The 256 x 256 tiles past their edges: channels beyond p (one, half a
     tile, a whole 128 x 128 quarter), tokens beyond n (a stage of 16 partly or
     wholly empty, a shorter last split), rows and bases that are not 16-byte
-    aligned, with a running sum; the last two shapes have too few products for
-    them and take the guarded 128 x 128 tiles.  The memory around X holds infinities, which
+    aligned, with a running sum; the last five shapes have too few products for
+    them (token-major 256 x 33 aside) and take the guarded 128 x 128 tiles.  The memory around X holds infinities, which
     any read past its end would carry into Sigma."""
     spec = synth.CONFIGS["c1"]
     X = synth.activations(spec, n=n, p=p)
@@ -246,6 +246,21 @@ def test_gram_ragged_wide_tiles(qe, oracle, p, n, layout, offset):
     # one rounding of each sum onto S0, besides the Gram's own bar
     assert rel_fro(S, oracle.gram(X) + S0) <= 1e-5
     assert np.array_equal(S, S.T)
+
+
+@pytest.mark.parametrize("p,n,layout,bf16", [
+    (384, 65536, 0, True), (384, 65536, 1, True),     # as many products either way, and no scale pass
+    (896, 8192, 0, True), (896, 8192, 1, True),       # unguarded 128 x 128 tiles, below 1e10
+    (512, 1025, 0, True), (768, 993, 0, True),        # rows not aligned, below 3e9
+    (500, 2048, 1, True), (512, 1024, 0, False), (512, 1025, 1, False), (700, 6200, 1, False),
+    (768, 5103, 0, False), (1152, 8192, 0, False)])
+def test_gram_default_products(qe, p, n, layout, bf16):
+    """Which products a default call takes: the bf16 split's, bit for bit, where its
+    128 x 128 tiles are the faster ones, else the fp16 split's (other roundings)."""
+    X = synth.gaussian((p, n), seed=7)
+    Xl = X if layout == 0 else np.ascontiguousarray(X.T)
+    same = np.array_equal(_gram(qe, Xl, layout), _gram(qe, Xl, layout, mode="bf16x3"))
+    assert same == bf16
 
 
 @pytest.mark.parametrize("layout", [0, 1])
