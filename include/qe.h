@@ -309,8 +309,9 @@ qe_status qe_objective(const float* W, const float* W_hat, const float* H, const
  * leading eigenvector), from fp64 sums, widened by a relative 2^-30 and
  * rounded up to fp32.
  * Synchronises `stream` every 32 iterations.  Up to p = 4096 those 32 run as one
- * cooperative launch that keeps Sigma in registers (where the runtime does not take
- * it, and beyond, one launch per iteration).
+ * cooperative launch that keeps Sigma in registers (where the runtime does not take it
+ * or a workgroup waits too long for another, one launch per iteration with the same
+ * result; beyond, one launch per iteration).
  * lambda_out: HOST float.
  * ------------------------------------------------------------------------ */
 size_t qe_lambda_workspace_size(int64_t p);

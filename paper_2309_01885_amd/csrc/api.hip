@@ -323,7 +323,18 @@ qe_status qe_lambda_max(const float* Sigma, int64_t p, int max_iters, float tol,
     if (!ws || ws_bytes < lambda_ws_bytes(p)) return QE_ERR_WORKSPACE;
     hipStream_t s = as_stream(stream);
     if (clear_status(ws, s) != QE_OK) return QE_ERR_HIP;
-    return launch_lambda(Sigma, p, max_iters, tol, lambda_out, ws, s);
+    return launch_lambda(Sigma, p, max_iters, tol, lambda_out, ws, kMaxPolls, s);
+}
+
+// qe_lambda_max with another bound on the on-chip form's waits (see launch_lambda): not
+// part of the ABI, for the tests of what follows when a wait gives up.
+qe_status qei_lambda_max_polls(const float* Sigma, int64_t p, int max_iters, float tol, float* lambda_out,
+                               void* ws, size_t ws_bytes, int max_polls, void* stream)
+{
+    if (!ws || ws_bytes < lambda_ws_bytes(p)) return QE_ERR_WORKSPACE;
+    hipStream_t s = as_stream(stream);
+    if (clear_status(ws, s) != QE_OK) return QE_ERR_HIP;
+    return launch_lambda(Sigma, p, max_iters, tol, lambda_out, ws, max_polls, s);
 }
 
 }  // extern "C"

@@ -503,12 +503,13 @@ __global__ __launch_bounds__(256) void power_last_kernel(const double* part, int
 // other ordering is needed.  Two buffers alternate; a workgroup writes iteration k + 1 only after it has read all of
 // k, when every other one has done with k - 1.  The launch is cooperative (all
 // workgroups resident), and a wait that lasts kMaxPolls polls gives up: the batch
-// then reports it and the call falls back to a launch per iteration.
+// then reports it and the call starts over with a launch per iteration of this same
+// kernel, where every word is there before it is read: the same sums in the same order,
+// so the result does not depend on what else the device was doing.
 // Bound by the exchange of y (about 2.7 us an iteration) and, at 4096, by the
 // conversions of the fp64 products: 12.7 -> 6.4 us an iteration at 4096 (Sigma, 67 MB,
 // streamed before), 6.7 -> 2.0 us at 1025, the call 5.0 -> 2.5 ms and 3.2 -> 1.0 ms.
 constexpr int64_t kChipMaxP = 4096;          // 256 workgroups of 128 values per lane
-constexpr int kMaxPolls = 1 << 20;
 
 __global__ __launch_bounds__(256) void power_clear_kernel(uint64_t* y, int64_t n, int* gave_up)
 {
@@ -519,7 +520,7 @@ __global__ __launch_bounds__(256) void power_clear_kernel(uint64_t* y, int64_t n
 
 template <int NC, int RW>
 __global__ __launch_bounds__(512, 1) void power_batch_kernel(const float* Sigma, int p, uint64_t* ybuf, int it0,
-                                                          int iters, double* part, int* gave_up)
+                                                          int iters, double* part, int* gave_up, int max_polls)
 {
     __shared__ __attribute__((aligned(16))) float y[256 * NC];
     __shared__ double wsum[8], wpart[8][3];
@@ -562,7 +563,7 @@ __global__ __launch_bounds__(512, 1) void power_batch_kernel(const float* Sigma,
                 }
 #pragma unroll
                 for (int v = 0; v < NV; ++v) late |= (uint32_t)(w[v] >> 32) != tag;
-            } while (late && ++polls < kMaxPolls);
+            } while (late && ++polls < max_polls);
         }
         double sq = 0.0;
 #pragma unroll
@@ -655,24 +656,33 @@ size_t lambda_ws_bytes(int64_t p)
     return b;
 }
 
-// Cooperative launch of one batch; false if the runtime does not take it.
+// One batch: as one cooperative launch (false if the runtime does not take it), or with
+// one launch per iteration.
 static bool launch_chip_batch(const float* Sigma, int p, uint64_t* ybuf, int it0, int iters, double* part,
-                              int* gave_up, hipStream_t s)
+                              int* gave_up, int max_polls, bool coop, hipStream_t s)
 {
     const void* f = p <= 512    ? reinterpret_cast<const void*>(power_batch_kernel<2, 1>)
                     : p <= 1024 ? reinterpret_cast<const void*>(power_batch_kernel<4, 1>)
                     : p <= 2048 ? reinterpret_cast<const void*>(power_batch_kernel<8, 1>)
                     : p <= 3072 ? reinterpret_cast<const void*>(power_batch_kernel<12, 2>)
                                 : reinterpret_cast<const void*>(power_batch_kernel<16, 2>);
-    void* args[] = {&Sigma, &p, &ybuf, &it0, &iters, &part, &gave_up};
-    if (hipLaunchCooperativeKernel(f, dim3((unsigned)chip_wgs(p)), dim3(512), args, 0, s) == hipSuccess)
-        return true;
-    (void)hipGetLastError();
-    return false;
+    const dim3 grid((unsigned)chip_wgs(p)), block(512);
+    if (coop) {
+        void* args[] = {&Sigma, &p, &ybuf, &it0, &iters, &part, &gave_up, &max_polls};
+        if (hipLaunchCooperativeKernel(f, grid, block, args, 0, s) == hipSuccess) return true;
+        (void)hipGetLastError();
+        return false;
+    }
+    int one = 1;
+    for (int b = 0; b < iters; ++b, ++it0, part += 3 * chip_wgs(p)) {
+        void* args[] = {&Sigma, &p, &ybuf, &it0, &one, &part, &gave_up, &max_polls};
+        if (hipLaunchKernel(f, grid, block, args, 0, s) != hipSuccess) return false;
+    }
+    return true;
 }
 
 qe_status launch_lambda(const float* Sigma, int64_t p, int max_iters, float tol, float* out,
-                        void* ws, hipStream_t s)
+                        void* ws, int max_polls, hipStream_t s)
 {
     Ws w(ws);
     const int64_t nwg = cdiv(p, kSymvRows);
@@ -680,27 +690,31 @@ qe_status launch_lambda(const float* Sigma, int64_t p, int max_iters, float tol,
     double* part[2] = {w.take<double>(3 * nwg), w.take<double>(3 * nwg)};
     double* hist = w.take<double>(2 * kLambdaCheck + 1);  // (rho, radius^2) per iteration; gave_up
     int* const gave_up = reinterpret_cast<int*>(hist + 2 * kLambdaCheck);
-    bool chip = p <= kChipMaxP;
+    const bool chip = p <= kChipMaxP;
+    bool coop = max_polls >= 0;
     uint64_t* ybuf = nullptr;
     double* cpart = nullptr;
     if (chip) {
         ybuf = w.take<uint64_t>(2 * kChipMaxP);
         cpart = w.take<double>(3 * chip_wgs(p) * kLambdaCheck);
+    }
+    auto clear = [&] {
         hipLaunchKernelGGL(power_clear_kernel, dim3((unsigned)cdiv(2 * kChipMaxP, 256)), dim3(256), 0, s,
                            ybuf, 2 * kChipMaxP, gave_up);
-    }
+    };
+    if (chip) clear();
     const int vec4 = (aligned16(Sigma) && p % 4 == 0) ? 1 : 0;
     double last = 0.0, prev = 0.0, last_r2 = 0.0;
     int it = 0, cur = 0;
     while (it < max_iters) {
         const int batch = std::min(kLambdaCheck, max_iters - it);
-        if (chip && !launch_chip_batch(Sigma, (int)p, ybuf, it, batch, cpart, gave_up, s)) {
-            chip = false;
-            it = 0;
-            last = 0.0;
-            continue;
-        }
         if (chip) {
+            if (!launch_chip_batch(Sigma, (int)p, ybuf, it, batch, cpart, gave_up,
+                                   coop ? max_polls : kMaxPolls, coop, s)) {
+                if (!coop) return QE_ERR_HIP;
+                coop = false;                            // not taken: from here launch by launch
+                continue;
+            }
             hipLaunchKernelGGL(power_hist_kernel, dim3((unsigned)batch), dim3(256), 0, s, cpart,
                                (int)chip_wgs(p), hist);
         } else {
@@ -720,9 +734,11 @@ qe_status launch_lambda(const float* Sigma, int64_t p, int max_iters, float tol,
         if (hipMemcpyAsync(h, hist, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess) return QE_ERR_HIP;
         if (hipStreamSynchronize(s) != hipSuccess) return QE_ERR_HIP;
         if (chip && *reinterpret_cast<const int*>(h + 2 * kLambdaCheck) != 0) {
-            chip = false;                                // a wait gave up: start over, launch by launch
+            if (!coop) return QE_ERR_HIP;
+            coop = false;                                // a wait gave up: start over, launch by launch
             it = 0;
             last = 0.0;
+            clear();
             continue;
         }
         // the first iteration of the batch whose quotient moved by <= tol relative

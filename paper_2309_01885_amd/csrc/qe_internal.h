@@ -498,7 +498,10 @@ qe_status launch_outliers_csr(const float* H, int64_t q, int64_t p, const int64_
                               const int64_t* nnz, int64_t cap, int64_t* rowptr, int32_t* cols,
                               float* vals, hipStream_t s);
 size_t lambda_ws_bytes(int64_t p);
+// max_polls: polls after which a wait of the on-chip form (p <= 4096) gives up; negative:
+// as if the runtime refused its cooperative launch.
+constexpr int kMaxPolls = 1 << 20;
 qe_status launch_lambda(const float* Sigma, int64_t p, int max_iters, float tol, float* out,
-                        void* ws, hipStream_t s);
+                        void* ws, int max_polls, hipStream_t s);
 
 }  // namespace qe

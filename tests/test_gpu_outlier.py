@@ -5,6 +5,8 @@ P_s on the same fp32 V is an integer decision taken in the same precision by
 both sides, so the support must be identical, ties and zeros included.
 End to end, E is fp32 on the GPU and fp64 in the oracle; the supports must
 still be identical on these seeds, and g must agree within 1e-4."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -296,6 +298,28 @@ def test_lambda_max_sizes(qe, p):
     ws = qe.workspace(qe.load().qe_lambda_workspace_size(p), "cuda")
     assert qe.lambda_max(Sd, max_iters=70, tol=1e-5, ws=ws) == lam
     assert qe.lambda_max(Sd, max_iters=70, tol=1e-5, ws=ws) == lam      # stale words in ws
+
+
+@pytest.mark.parametrize("p", [7, 512, 1025, 2500, 4096])
+def test_lambda_max_without_the_cooperative_launch(qe, p):
+    """Where the cooperative launch is refused (-1) or its waits give up (after one poll:
+    some workgroup always comes early), the call goes on or starts over with a launch per
+    iteration and returns the same value bit for bit."""
+    X = synth.correlated_activations(p, 96, 0.9, 5, out_channels=max(1, p // 200), out_mult=8.0)
+    S = dev((X.astype(np.float64) @ X.T.astype(np.float64)).astype(np.float32))
+    lib = qe.load()
+    ws = qe.workspace(lib.qe_lambda_workspace_size(p), "cuda")
+    fn = lib.qei_lambda_max_polls
+    fn.restype = ctypes.c_int
+    for iters, tol in ((100, 1e-6), (37, 0.0)):
+        want = qe.lambda_max(S, max_iters=iters, tol=tol)
+        for polls in (-1, 0, 1 << 20):
+            got = ctypes.c_float()
+            torch.cuda.synchronize()
+            assert fn(ctypes.c_void_p(S.data_ptr()), ctypes.c_int64(p), iters, ctypes.c_float(tol),
+                      ctypes.byref(got), ctypes.c_void_p(ws.data_ptr()), ctypes.c_size_t(ws.numel()),
+                      polls, ctypes.c_void_p(0)) == 0
+            assert got.value == want, (iters, polls)
 
 
 def test_lambda_max_two_threads(qe):
