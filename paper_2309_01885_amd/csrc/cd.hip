@@ -1143,7 +1143,7 @@ qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, in
     const int period = (int)((flags & QE_RELAX_MASK) >> 8);
     bool prev_relaxed = false;
     const double* const f0 = f_prev;
-    const bool rows = !base.dense && !base.fp32 && period == 0 && cd_rows_fits(p);
+    const bool rows = !base.dense && !base.fp32 && period == 0 && cd_rows_fits(q, p);
     const bool warm = since_init < 0;    // from codes that the caller brought
     const int limit = rows ? cd_rows_limit(q, p, warm) : -1;
     const bool large = (double)q * (double)p * (double)p >= kManyWork;

@@ -345,7 +345,9 @@ constexpr int64_t kRowsMaxP = 16384;     // 16 waves of 1024 columns
 constexpr int64_t kOneWave = 1024;       // up to here one wave holds a row
 constexpr int kSampleRows = 256;
 
-bool cd_rows_fits(int64_t p) { return p <= kRowsMaxP; }
+static int rows_threads(int64_t p) { return p <= kOneWave ? 64 : (int)(64 * cdiv(p, 1024)); }
+
+bool cd_rows_fits(int64_t q, int64_t p) { return p <= kRowsMaxP && q <= max_grid(rows_threads(p)); }
 
 // The most moves in the sample with which the row form is taken, or -1: always.
 // The row form costs 4 p bytes per move, at 9 TB/s while Sigma fits the die-level
@@ -405,7 +407,7 @@ qe_status launch_cd_rows(const float* Sigma, int64_t q, int64_t p, const float* 
                    first, opt1, obj ? fpart : nullptr, status};
         const dim3 grid((unsigned)q);
 #define QE_ROWS(G, M) \
-    hipLaunchKernelGGL((cd_rows_kernel<G, M>), grid, dim3((unsigned)(64 * cdiv(p, 256 * G))), 0, s, a)
+    hipLaunchKernelGGL((cd_rows_kernel<G, M>), grid, dim3((unsigned)rows_threads(p)), 0, s, a)
         if (p <= 256) QE_ROWS(1, false);
         else if (p <= 512) QE_ROWS(2, false);
         else if (p <= kOneWave) QE_ROWS(4, false);

@@ -217,7 +217,9 @@ __global__ __launch_bounds__(2 * TILE, TILE == 256 ? 1 : 2) void quad_kernel(Qua
     __shared__ __attribute__((aligned(16))) uint32_t lds[TILE == 256 ? kX3wLdsDw : kX3LdsDw];
     __shared__ double sh[TILE / 32];
     // rows fastest: the workgroups at work at one time share their run of Sigma
-    const int64_t unit = blockIdx.x / (2 * a.tm), slot = blockIdx.x % (2 * a.tm);
+    const int64_t wg = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    const int64_t unit = wg / (2 * a.tm), slot = wg % (2 * a.tm);
+    if (unit >= a.units) return;                  // uniform: the whole workgroup leaves
     const bool isw = slot >= a.tm;
     const int64_t row0 = (slot - (isw ? a.tm : 0)) * TILE;
     // whole runs first, those of the same K tiles side by side (they share their
@@ -325,7 +327,7 @@ qe_status launch_objective(const float* W, const float* Wh, const float* H, cons
     const int64_t n = pl.tm * pl.units;
     double* part = w.take<double>(2 * n);
     const QuadArgs a{Wh, H, W, Sigma, q, p, pl.tm, pl.tn, pl.full, pl.units, pl.chunk, part, status};
-    const dim3 grid((unsigned)(2 * n)), block((unsigned)(2 * pl.tile));
+    const dim3 grid = grid_xy(2 * n, 2 * pl.tile), block((unsigned)(2 * pl.tile));
     if (pl.tile == 256 && H)
         hipLaunchKernelGGL((quad_kernel<256, true>), grid, block, 0, s, a);
     else if (pl.tile == 256)

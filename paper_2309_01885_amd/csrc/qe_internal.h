@@ -446,6 +446,15 @@ struct Ws {
     }
 };
 
+// The most workgroups of a launch along x: the runtime takes fewer than 2^32 threads.
+inline int64_t max_grid(int threads) { return ((int64_t(1) << 32) - 1) / threads; }
+// At least wgs workgroups, number blockIdx.y * gridDim.x + blockIdx.x, as few as possible.
+inline dim3 grid_xy(int64_t wgs, int threads)
+{
+    const int64_t y = cdiv(wgs, max_grid(threads));
+    return dim3((unsigned)cdiv(wgs, y), (unsigned)y);
+}
+
 // Launch helpers implemented in the kernel translation units (host side).
 size_t gram_ws_bytes(int64_t p, int64_t n);
 qe_status launch_gram(const float* X, int64_t p, int64_t n, int layout, float* Sigma,
@@ -466,7 +475,7 @@ qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, in
 // Which sweeps of a call run row by row: the sample being counted (workgroups that have
 // counted, from bit 40 on, and their moves) and the first sweep that does (device memory).
 struct RowsChoice { unsigned long long count; int first; };
-bool cd_rows_fits(int64_t p);
+bool cd_rows_fits(int64_t q, int64_t p);
 int cd_rows_limit(int64_t q, int64_t p, bool warm);
 qe_status launch_cd_sample(const float* R, const float* Wh, const float* inv_d, const float* scale,
                            const float* zero, const float* inv_s, int64_t q, int64_t p, float maxq,

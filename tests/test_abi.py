@@ -236,6 +236,16 @@ def test_cd_sweep_noalloc_argument_errors(lib):
     assert L.qe_cd_workspace_size(14848, 59392, 0) <= (64 << 20)   # the largest workload fits
 
 
+def test_rows_form_stays_inside_the_launch_limits(lib):
+    """One workgroup per row: fewer than 2^32 threads in a launch, whatever the rows hold."""
+    fits = lib[0]._ZN2qe12cd_rows_fitsEll
+    fits.restype = ctypes.c_bool
+    fits.argtypes = [ctypes.c_int64, ctypes.c_int64]
+    for p, threads in ((1, 64), (1024, 64), (1025, 128), (4096, 256), (16384, 1024)):
+        assert fits((2 ** 32 - 1) // threads, p) and not fits(2 ** 32 // threads, p)
+    assert not fits(1, 16385)
+
+
 def test_lambda_and_objective_argument_errors(lib):
     L, _ = lib
     f = L.qe_lambda_max

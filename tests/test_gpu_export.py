@@ -62,3 +62,24 @@ def test_outliers_csr_row_search(qe, q, p, n):
     assert np.array_equal(host(rowptr), np.searchsorted(lin, np.arange(q + 1) * p))
     assert np.array_equal(host(cols), lin % p)
     assert np.array_equal(host(vals), H.reshape(-1)[lin])
+
+
+def test_more_rows_than_one_grid_dimension(qe):
+    """Row counts whose workgroups hold 2^32 threads and more: CSR row pointers (16
+    lanes per row), the objective's row tiles (two forms of 128 rows each)."""
+    q = 2 ** 28 + 7
+    H = torch.zeros((q, 1), device="cuda")
+    at = torch.tensor([5, q - 8, q - 1], device="cuda")
+    H[at, 0] = torch.tensor([1.0, 2.0, 3.0], device="cuda")
+    rowptr, cols, vals = qe.outliers_csr(H, at, torch.tensor([3], device="cuda"))
+    assert [int(rowptr[i]) for i in (0, 5, 6, q - 8, q - 7, q - 1, q)] == [0, 0, 1, 1, 2, 2, 3]
+    assert int(rowptr.double().sum()) == (q - 7 - 6) + 2 * 7 + 3
+    assert host(vals).tolist() == [1.0, 2.0, 3.0] and not np.any(host(cols))
+    del H, rowptr
+    torch.cuda.empty_cache()
+    q = 2 ** 30 + 5
+    W, Wh = torch.ones((q, 1), device="cuda"), torch.full((q, 1), 3.0, device="cuda")
+    out = qe.objective(W, Wh, torch.full((1, 1), 0.5, device="cuda"))
+    assert host(out).tolist() == [2.0 * q, 0.5 * q]
+    del W, Wh
+    torch.cuda.empty_cache()
