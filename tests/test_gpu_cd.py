@@ -149,13 +149,23 @@ def test_tiny_layers(qe, oracle, q, p):
     check_parity(oracle, W, S32, 3, scale, zero, g, f"tiny {q}x{p}")
 
 
+def blocked(qe):
+    """Keeps every sweep of a call in the blocked form, with code differences and
+    sparse block updates and, in calls of fewer than 255 sweeps, without a relaxed one
+    (a call with QE_RELAX_PERIOD has no row form)."""
+    return qe.QE_RELAX_PERIOD(255)
+
+
+@pytest.mark.parametrize("form", ["default", "blocked"])
 @pytest.mark.parametrize("block", [16, 32, 64, 128])
-def test_block_width_invariance(qe, oracle, block):
+def test_block_width_invariance(qe, oracle, block, form):
+    """By default only the first sweep of so small a layer runs blocked; the blocked
+    form of the later ones works on code differences."""
     W, X = layer(96, 250, 1024, 12, corr=0.9)
     S32 = oracle.damp(oracle.gram(X), 0.01).astype(np.float32)
     scale, zero = oracle.grid_minmax(W, 4)
-    g = gpu_cd(qe, W, S32, 4, scale, zero, 4, block=block)
-    check_parity(oracle, W, S32, 4, scale, zero, g, f"block {block}")
+    g = gpu_cd(qe, W, S32, 4, scale, zero, 4, block=block, extra=blocked(qe) if form == "blocked" else 0)
+    check_parity(oracle, W, S32, 4, scale, zero, g, f"block {block} {form}")
 
 
 def test_multi_sweep_call_equals_resumed_calls(qe, oracle):
@@ -247,17 +257,19 @@ def block_update_regimes(hist, q, p, tile=128, super_w=256, rows_max=64, row_nz_
 
 @pytest.mark.parametrize("q,p", [(512, 1024), (300, 777)])
 def test_sparse_block_update(qe, oracle, q, p):
-    """From the second sweep on, a block-update tile whose rows changed few
-    codes applies only the nonzero code differences (QE_CD_DENSE turns this
-    off).  Over 12 sweeps the run passes from dense to sparse tiles (checked
-    from the codes); every sweep meets the parity bar against the oracle and
-    leaves R = (What - W) Sigma to fp32 rounding, and the matrix-core-only
-    run reaches the same objective."""
+    """From the second sweep on, a block-update tile of the blocked form whose rows
+    changed few codes applies only the nonzero code differences (QE_CD_DENSE
+    turns this off).  Over 12 sweeps the run passes from dense to sparse tiles
+    (worked out from the codes; that they ran shows in R, which rounds otherwise
+    than in the row form and with QE_CD_DENSE); every sweep meets the parity bar
+    against the oracle and leaves R = (What - W) Sigma to fp32 rounding, and the
+    matrix-core-only run reaches the same objective.  777 channels: rows of R and Sigma that
+    are not 8-byte aligned, and an odd last column."""
     W, X = layer(q, p, 2048, 43, corr=0.9)
     S32 = oracle.damp(oracle.gram(X), 0.01).astype(np.float32)
     scale, zero = oracle.grid_minmax(W, 4)
     sweeps = 12
-    g = gpu_cd(qe, W, S32, 4, scale, zero, sweeps)
+    g = gpu_cd(qe, W, S32, 4, scale, zero, sweeps, extra=blocked(qe))
     regimes = block_update_regimes(g["hist"], q, p)
     print(f"{q}x{p}: (sparse, dense) block updates per sweep 2..{sweeps}: {regimes}")
     assert regimes[0][1] > 0                              # sweep 2: dense tiles
@@ -270,6 +282,11 @@ def test_sparse_block_update(qe, oracle, q, p):
         assert np.all(np.abs(g["Rs"][k] - D @ S64) <= bound), f"sweep {k + 1}"
     d = gpu_cd(qe, W, S32, 4, scale, zero, sweeps, extra=qe.QE_CD_DENSE)
     check_parity(oracle, W, S32, 4, scale, zero, d, f"dense {q}x{p}")
+    # the same codes and another rounding of R in a sweep: another form of the update
+    rows = gpu_cd(qe, W, S32, 4, scale, zero, sweeps)
+    for other in (d, rows):
+        first = next(k for k in range(sweeps) if not np.array_equal(g["Rs"][k], other["Rs"][k]))
+        assert first > 0 and np.array_equal(g["hist"][first - 1], other["hist"][first - 1])
     assert d["obj"][-1] == pytest.approx(g["obj"][-1], rel=1e-6)
 
 
