@@ -107,6 +107,42 @@ def test_fixed_point_and_no_objective(qe, oracle):
     assert np.array_equal(host(R), before) and np.array_equal(host(codes), g["codes"])
 
 
+def test_more_sweeps_than_one_launch(qe, oracle):
+    """With an objective a launch of the row form takes 128 sweeps; the next one starts
+    from the state and the objective that it left.  Slowly settling rows (8 bits, from
+    codes far off, rho = 0.995): still moving behind the 128th sweep and behind the
+    256th.  The same state without an objective (one launch), and in two calls.  (Fewer
+    than 16 rows: the row form from the first sweep on.)"""
+    q, p, sweeps = 8, 1100, 300
+    W, S32 = synth.gaussian((q, p), seed=57, std=0.02), ar1(p, 0.995)
+    scale, zero = oracle.grid_minmax(W, 8)
+    c0 = synth.integers((q, p), seed=58, lo=0, hi=256)
+    W0 = oracle.dequant(c0, scale, zero).astype(np.float32)
+    Wd, Sd, sc, ze = dev(W), dev(S32), dev(scale), dev(zero)
+
+    def run(*calls, with_obj=True, extra=0):
+        Wh, codes = dev(W0), dev(c0.astype(np.uint8))
+        R, out, flags = torch.empty_like(Wd), [], qe.QE_CODES_VALID
+        for k in calls:
+            obj = torch.zeros(k, dtype=torch.float64, device="cuda")
+            if out:
+                obj[0] = out[-1]
+                flags |= qe.QE_OBJ_IN
+            qe.cd_sweep(Wd, Sd, 8, sc, ze, Wh, codes, R, k, flags=flags | extra,
+                        obj=obj if with_obj else None)
+            flags = qe.QE_R_VALID | qe.QE_CODES_VALID
+            out += host(obj).tolist()
+        return host(codes), host(Wh), host(R), out
+    codes, Wh, R, f = run(sweeps)
+    assert all(a >= b for a, b in zip(f, f[1:]))
+    assert f[126] > f[127] > f[128] > f[130] and f[255] > f[256] > f[260]
+    for got in (run(sweeps, with_obj=False), run(100, 200)):
+        assert np.array_equal(got[0], codes) and np.array_equal(got[1], Wh) and np.array_equal(got[2], R)
+    assert got[3] == f
+    assert not np.array_equal(run(sweeps, extra=qe.QE_RELAX_PERIOD(255))[2], R)     # the blocked form's
+    assert f[-1] == pytest.approx(oracle.objective(W, Wh, S32), rel=1e-4)
+
+
 @pytest.mark.parametrize("dense", [False, True])
 @pytest.mark.parametrize("q,p", [(17, 257), (150, 301), (129, 640), (260, 1027)])
 def test_alignment_changes_nothing(qe, oracle, q, p, dense):
