@@ -289,6 +289,8 @@ qe_status qe_topk_columns(const float* V, int64_t q, int64_t p, int64_t c, float
  * calibration error), recomputed from scratch, independent of R:
  *   out[0] = <D, D Sigma> = ||(What + H - W) X||_F^2,  D = What + H - W,
  *   out[1] = <W, W Sigma> = ||W X||_F^2.
+ * Sigma has to be symmetric: only its lower half is read (and whole tiles of up to 256
+ * channels along the diagonal), doubled; another matrix gives another number.
  * The products D Sigma use the exact three-way bf16 split (see qe_gram);
  * <D, D Sigma> is summed in fp64.  H may be NULL.  out: device, 2 doubles.
  * ------------------------------------------------------------------------ */

@@ -1,8 +1,11 @@
 """qe_objective (Sec. 2.1 problem (1)) against fp64 sums of the same numbers, at
 the edges of its tiles (128 and 256) and of its runs over K.  Bound: every
-product is good to 2^-23 of itself and is added into fp32 sums of at most 1024
-products, whose roundings are below 1024 * 2^-24 of the sum of magnitudes and
-random in sign; 2^-20 of the sum of magnitudes covers both with room."""
+product is good to 2^-23 of itself and is added into an fp32 sum of at most n = p and at
+most 32 * 256 products (the longest run of tiles).  Its roundings, each below 2^-24 of
+the sum so far and random in sign, come to about sqrt(n) 2^-24 <= 2^-17.5 of its sum of
+magnitudes, and the q p running sums of a form, whose errors are independent, to
+sqrt(n / (q p)) 2^-24 <= 2^-24 / sqrt(q) of the form's: 2^-20 of the sum of magnitudes
+covers both with room."""
 import numpy as np
 import pytest
 import torch
@@ -32,6 +35,22 @@ def test_objective_matches_fp64(qe, q, p, outliers):
         A, S64 = A.astype(np.float64), S.astype(np.float64)
         ref = np.sum(A * (A @ S64))
         mag = np.sum(np.abs(A) * (np.abs(A) @ np.abs(S64)))
+        assert abs(got - ref) <= 2.0 ** -20 * mag, (got, ref, mag)
+
+
+def test_objective_long_runs(qe):
+    """2048 x 8448: column tiles of up to 33 tiles of K in runs of 32 (8192 products in
+    an fp32 sum) and a second run of one tile, against fp64 products on the device."""
+    q, p = 2048, 8448
+    W, Wh = dev(synth.gaussian((q, p), seed=68)), dev(synth.gaussian((q, p), seed=69))
+    a = torch.arange(p, device="cuda")
+    S = torch.where((a[:, None] // 7 + a[None, :] // 7) % 3 == 0, 1.0, -0.5) * (
+        0.999 ** (a[:, None] - a[None, :]).abs().float())
+    out = host(qe.objective(W, Wh, S))
+    S64 = S.double()
+    for got, A in zip(out, ((Wh - W).double(), W.double())):
+        ref = float((A * (A @ S64)).sum())
+        mag = float((A.abs() * (A.abs() @ S64.abs())).sum())
         assert abs(got - ref) <= 2.0 ** -20 * mag, (got, ref, mag)
 
 
