@@ -236,7 +236,7 @@ struct X3Col {
 // wm * 64 + 32 mi and columns wn * 64 + 32 ni (mi, ni < 2).  NP = 6: both
 // operands split in three (the six kept products); NP = 3: A exact in bf16
 // (its h plane only), B split in three, all three products exact.
-template <int NP = 6>
+template <int NP>
 __device__ __forceinline__ void x3_mfma_stage(const uint32_t* sA, const uint32_t* sB,
                                               f32x16 (&acc)[2][2])
 {
@@ -303,8 +303,9 @@ __device__ __forceinline__ void x3_interleave()
 }
 
 // acc += A[row0a.., 0..K) B[row0b.., 0..K)^T on the 128 x 128 tile of 256
-// threads for operands whose 128-row panels lie inside the matrix, with K a
-// positive multiple of 32 and aligned rows.  Global loads run two stages ahead
+// threads, with K a positive multiple of 32 (operands of panels that reach past the
+// matrix, of short last stages or of unaligned rows guard their own load_full: XRowQ,
+// X3Quad of the objective).  Global loads run two stages ahead
 // of the matrix cores; every load is unconditional so that the wait before a
 // stage's LDS store leaves the next stage's loads in flight.  `lds` holds
 // kX3LdsDw dwords.  Ends with a barrier.  INTERLEAVE pays off in long K loops
@@ -357,9 +358,9 @@ __device__ __forceinline__ void nt_tile_x3_full(const OA& A, int64_t row0a, cons
     __syncthreads();
 }
 
-// Any shape: guarded loads (out-of-range elements read as 0), one stage of
+// Any shape: guarded loads (out-of-range elements read as 0), six products, one stage of
 // prefetch.  Ends with a barrier.
-template <int NP = 6, class OA, class OB>
+template <class OA, class OB>
 __device__ __forceinline__ void nt_tile_x3_edge(const OA& A, int64_t row0a, const OB& B, int64_t row0b,
                                        int64_t K, uint32_t* lds, f32x16 (&acc)[2][2])
 {
@@ -380,7 +381,7 @@ __device__ __forceinline__ void nt_tile_x3_edge(const OA& A, int64_t row0a, cons
             A.load(row0a, (c + 1) * kX3KC, sa);
             B.load(row0b, (c + 1) * kX3KC, sb);
         }
-        x3_mfma_stage<NP>(a0, b0, acc);
+        x3_mfma_stage<6>(a0, b0, acc);
         if (more) {
             A.store(a1, sa);
             B.store(b1, sb);
@@ -392,7 +393,7 @@ __device__ __forceinline__ void nt_tile_x3_edge(const OA& A, int64_t row0a, cons
             A.load(row0a, (c + 2) * kX3KC, sa);
             B.load(row0b, (c + 2) * kX3KC, sb);
         }
-        x3_mfma_stage<NP>(a1, b1, acc);
+        x3_mfma_stage<6>(a1, b1, acc);
         if (more) {
             A.store(a0, sa);
             B.store(b0, sb);
@@ -527,8 +528,8 @@ __device__ __forceinline__ void x3w_stage3(const OA& A, int64_t row0a, const OB&
 }
 
 // acc += A[row0a.., 0..K) B[row0b.., 0..K)^T on the 256 x 256 tile of 512
-// threads; K a positive multiple of 32, every 256-row panel inside the matrix,
-// aligned rows.  `lds` holds kX3wLdsDw dwords.  Ends with a barrier.
+// threads; K a positive multiple of 32.  Operands of panels that reach past the matrix,
+// of short last stages or of unaligned rows guard their own load_full.  `lds` holds kX3wLdsDw dwords.  Ends with a barrier.
 template <class OA, class OB>
 __device__ __forceinline__ void nt_tile_x3_wide(const OA& A, int64_t row0a, const OB& B, int64_t row0b,
                                                 int64_t K, uint32_t* lds, f32x16 (&acc)[2][4])
