@@ -83,6 +83,47 @@ __device__ __forceinline__ void apply_move(f32x4 (&L)[G], const float* srow, int
         for (int e = 0; e < 4; ++e) L[g][e] = fmaf(delta, v[g][e], L[g][e]);
 }
 
+// Moves [k, k + N) of another wave's turn, all their rows of Sigma in flight together.
+template <int G, bool FULL, int N>
+__device__ __forceinline__ void apply_listed(f32x4 (&L)[G], const RowsArgs& a, const int2* li, int k, int c0)
+{
+    f32x4 v[N][G];
+    float delta[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const int2 en = li[k + u];
+        const float* srow = a.Sigma + (int64_t)__builtin_amdgcn_readfirstlane(en.x) * a.p;
+        delta[u] = __int_as_float(en.y);
+#pragma unroll
+        for (int g = 0; g < G; ++g) v[u][g] = load4<FULL>(srow, c0 + 256 * g, (int)a.p);
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) L[g][e] = fmaf(delta[u], v[u][g][e], L[g][e]);
+}
+
+// The moves of another wave's turn, in order; AHEAD: four of them at a time.
+template <int G, bool FULL, bool AHEAD>
+__device__ __forceinline__ void apply_list(f32x4 (&L)[G], const RowsArgs& a, const int2* li, int cnt, int c0)
+{
+    int k = 0;
+    if constexpr (AHEAD) {
+        for (; k + 4 <= cnt; k += 4) apply_listed<G, FULL, 4>(L, a, li, k, c0);
+        if (k + 2 <= cnt) {
+            apply_listed<G, FULL, 2>(L, a, li, k, c0);
+            k += 2;
+        }
+    }
+    for (; k < cnt; ++k) {
+        const int2 en = li[k];
+        const int j = __builtin_amdgcn_readfirstlane(en.x);
+        apply_move<G, FULL>(L, a.Sigma + (int64_t)j * a.p, c0, (int)a.p, __int_as_float(en.y));
+    }
+}
+
 // One group of 256 columns of the wave's turn.  Returns the number of moves so far.
 // KEEP: the group's codes stay unpacked over its moves (four more registers, which
 // cost workgroups of many waves one of two places on a CU: 2.3 -> 2.9 ms for a
@@ -163,7 +204,7 @@ __device__ __forceinline__ int take_turn(std::integer_sequence<int, g...>, const
 }
 
 // MULTI: several waves per row, 1024 columns each; else one wave.
-template <int G, bool MULTI>
+template <int G, bool MULTI, bool AHEAD>
 __global__ __launch_bounds__(MULTI ? 1024 : 64) void cd_rows_kernel(RowsArgs a)
 {
     if (failed(a.status)) return;
@@ -215,19 +256,10 @@ __global__ __launch_bounds__(MULTI ? 1024 : 64) void cd_rows_kernel(RowsArgs a)
             const int cnt = count[turn];
             moves += cnt;
             if (wave != w) {
-                if (full) {
-                    for (int k = 0; k < cnt; ++k) {
-                        const int2 en = li[k];
-                        const int j = __builtin_amdgcn_readfirstlane(en.x);
-                        apply_move<G, true>(L, a.Sigma + (int64_t)j * a.p, c0, n, __int_as_float(en.y));
-                    }
-                } else if (wcol < n) {
-                    for (int k = 0; k < cnt; ++k) {
-                        const int2 en = li[k];
-                        const int j = __builtin_amdgcn_readfirstlane(en.x);
-                        apply_move<G, false>(L, a.Sigma + (int64_t)j * a.p, c0, n, __int_as_float(en.y));
-                    }
-                }
+                if (full)
+                    apply_list<G, true, AHEAD>(L, a, li, cnt, c0);
+                else if (wcol < n)
+                    apply_list<G, false, AHEAD>(L, a, li, cnt, c0);
             }
         }
         if (a.fpart) {
@@ -344,6 +376,13 @@ __global__ __launch_bounds__(256) void cd_sample_kernel(const float* __restrict_
 constexpr int64_t kRowsMaxP = 16384;     // 16 waves of 1024 columns
 constexpr int64_t kOneWave = 1024;       // up to here one wave holds a row
 constexpr int kSampleRows = 256;
+// Layers of few rows apply another wave's moves four at a time: nothing but the loads in
+// flight hides the latency of a row of Sigma there (384 x 1792, five sweeps of a layer of
+// 1472 tokens: 1.73 -> 1.65 ms, 1003 x 3001, rho = 0.9, ten sweeps 1.84 -> 1.67, 300 x 6000
+// 2.74 -> 2.58).  That takes 125 registers, four waves per SIMD; where the workgroups then
+// no longer fit the chip at once, more waves hide it better (1282 x 3000 1.36 against
+// 1.53 ms, 768 x 5000, whose five waves load the SIMDs unevenly, 2.72 against 3.11).
+constexpr int kCus = 256, kAheadWavesPerSimd = 4;
 
 static int rows_threads(int64_t p) { return p <= kOneWave ? 64 : (int)(64 * cdiv(p, 1024)); }
 
@@ -406,12 +445,13 @@ qe_status launch_cd_rows(const float* Sigma, int64_t q, int64_t p, const float* 
         RowsArgs a{Sigma, inv_d, scale, zero, inv_s, Wh, codes, R, q, p, maxq, k, std::min(k + per, sweeps),
                    first, opt1, obj ? fpart : nullptr, status};
         const dim3 grid((unsigned)q);
-#define QE_ROWS(G, M) \
-    hipLaunchKernelGGL((cd_rows_kernel<G, M>), grid, dim3((unsigned)rows_threads(p)), 0, s, a)
-        if (p <= 256) QE_ROWS(1, false);
-        else if (p <= 512) QE_ROWS(2, false);
-        else if (p <= kOneWave) QE_ROWS(4, false);
-        else QE_ROWS(4, true);
+#define QE_ROWS(G, M, A) \
+    hipLaunchKernelGGL((cd_rows_kernel<G, M, A>), grid, dim3((unsigned)rows_threads(p)), 0, s, a)
+        if (p <= 256) QE_ROWS(1, false, false);
+        else if (p <= 512) QE_ROWS(2, false, false);
+        else if (p <= kOneWave) QE_ROWS(4, false, false);
+        else if (q <= kCus * (kAheadWavesPerSimd / cdiv(rows_threads(p), 256))) QE_ROWS(4, true, true);
+        else QE_ROWS(4, true, false);
 #undef QE_ROWS
         if (obj)
         {

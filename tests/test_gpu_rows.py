@@ -88,6 +88,36 @@ def test_warm_start_that_keeps_moving(qe, oracle, q, p):
     assert one["obj"] == g["obj"] == want["obj"]
 
 
+def few_tokens(p, n, seed):
+    """Damped Gram matrix of n random tokens, exactly symmetric (on the device): the fewer
+    tokens per channel, the more codes a sweep moves."""
+    X = dev(synth.gaussian((p, n), seed=seed))
+    S = X @ X.T / n
+    S = (S + S.T) / 2
+    S.diagonal().add_(0.01)
+    return S.contiguous()
+
+
+@pytest.mark.parametrize("q,p", [(1030, 1101), (1030, 2304), (1030, 3075), (520, 4100)])
+def test_few_rows_round_as_many(qe, q, p):
+    """Rows are independent: those of a layer small enough to apply another wave's moves
+    several at a time end bit for bit as within a layer that applies them one by one."""
+    W, S = dev(synth.gaussian((q, p), seed=59, std=0.02)), few_tokens(p, 4 * p, 60)
+    scale, zero = qe.grid_minmax(W, 4)
+    Wh, R, codes = torch.empty_like(W), torch.empty_like(W), torch.zeros((q, p), dtype=torch.uint8, device="cuda")
+    qe.cd_sweep(W, S, 4, scale, zero, Wh, codes, R, 2, flags=qe.QE_INIT_FROM_W)
+    n = q - 20
+    few = [t[:n].clone() for t in (Wh, codes, R)]
+    flags = qe.QE_R_VALID | qe.QE_CODES_VALID
+    before = codes.clone()
+    qe.cd_sweep(W, S, 4, scale, zero, Wh, codes, R, 2, flags=flags)
+    qe.cd_sweep(W[:n], S, 4, scale[:n], zero[:n], few[0], few[1], few[2], 2, flags=flags)
+    moves = float((codes != before)[:n].float().sum(1).mean())
+    assert 16 < moves < 0.1 * p, moves               # lists of many moves, below the line
+    for a, b in zip(few, (Wh, codes, R)):
+        assert torch.equal(a, b[:n])
+
+
 def test_fixed_point_and_no_objective(qe, oracle):
     """Rows that stop moving leave the later sweeps early: the objective stays,
     and a call without one gives the same state."""
