@@ -994,13 +994,8 @@ __global__ __launch_bounds__(256, 2) void cd_step_kernel(StepArgs a)
 // columns).  From codes that the caller brings, any sweep may move most of them:
 // every one is sampled (4096 x 4096, rho = 0.9, from rounded weights, 13 to 17% of the
 // codes move for ten sweeps: 26.6 ms with the row form from the fifth sweep on, 11.3
-// so).  From What = W the first sweep leaves few: 10 to 30% move in the second, 1 to
-// 3.5% in the fifth, on every layer, bit width and conditioning tried, and there the
-// row form took at most 1.15 times the blocked sweep (large layers: the line lies
-// lower, and the launches weigh less).  So the choice is offered for its first sweeps.
-constexpr int kFewOptional = 4;          // sweeps 1 .. 3 after What = W
-constexpr int kManyOptional = 8;         // with at least kManyWork
-constexpr double kManyWork = 1.5e11;     // q p^2
+// so).  From What = W the later ones move few, and the choice is offered for the first of
+// them (cd_rows_offered).
 constexpr int kChoiceWord = 16;          // RowsChoice, in the status region
 static_assert(kChoiceWord * sizeof(int) + sizeof(RowsChoice) <= kStatusBytes, "the choice fits");
 
@@ -1145,8 +1140,8 @@ qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, in
     const double* const f0 = f_prev;
     const bool rows = !base.dense && !base.fp32 && period == 0 && cd_rows_fits(q, p);
     const bool warm = since_init < 0;    // from codes that the caller brought
-    const int limit = rows ? cd_rows_limit(q, p, warm) : -1;
-    const bool large = (double)q * (double)p * (double)p >= kManyWork;
+    const int limit = rows ? cd_rows_limit(q, p) : -1;
+    const int offered = rows ? cd_rows_offered(q, p) : 0;
     int opt0 = -1, opt1 = -1;            // with rows: sweeps from valid codes, optional ones [opt0, opt1)
     for (int sw = 0; sw < sweeps; ++sw) {
         const int k = sw + 1;
@@ -1162,7 +1157,7 @@ qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, in
         prev_relaxed = base.relax != 0;
         if (rows && base.intd) {
             if (opt0 < 0) opt0 = opt1 = sw;
-            if (limit < 0 || (!warm && since_init + sw >= (large ? kManyOptional : kFewOptional))) break;
+            if (limit < 0 || (!warm && since_init + sw >= offered)) break;
             // optional: these launches do nothing when few coordinates move
             if (launch_cd_sample(R, Wh, inv_d, scale, zero, inv_s, q, p, base.maxq, sw, limit, choice, status,
                                  s) != QE_OK)

@@ -388,6 +388,19 @@ static int rows_threads(int64_t p) { return p <= kOneWave ? 64 : (int)(64 * cdiv
 
 bool cd_rows_fits(int64_t q, int64_t p) { return p <= kRowsMaxP && q <= max_grid(rows_threads(p)); }
 
+constexpr double kFewRows = 0.12;
+constexpr double kManyWork = 1.5e11;     // q p^2
+
+// The share of moves at which the blocked sweep costs what the bytes of the row form do
+// (see cd_rows_limit).
+static double rows_line(int64_t q, int64_t p)
+{
+    const double work = (double)q * (double)p * (double)p;
+    const double bw = 4.0 * (double)p * (double)p <= 2.0e8 ? 9.0e12 : 7.0e12;
+    const double dense = std::max(2.0 * work / 135.0e12, (double)(cdiv(p, 256) + 1) * 50.0e-6);
+    return dense * bw / (4.0 * work);
+}
+
 // The most moves in the sample with which the row form is taken, or -1: always.
 // The row form costs 4 p bytes per move, at 9 TB/s while Sigma fits the die-level
 // cache and 7 TB/s beyond; the blocked form its products, at 135 TFLOP/s (fp32
@@ -403,24 +416,36 @@ bool cd_rows_fits(int64_t q, int64_t p) { return p <= kRowsMaxP && q <= max_grid
 // search's chain does: 20 us and 0.45 us per move for one wave (128 x 300, 56%: 0.11
 // against 0.08 ms; 16 x 1024, 59%: 0.27 against 0.15), 0.87 us for several (16 x 4096,
 // 62%: 2.24 against 0.56 ms; 64 x 12000, 74%: 7.5 against 1.8), and 38 us for 256
-// columns of the blocked form.  Only codes that the caller brings (warm) move so many:
-// after What = W such a layer is always taken row by row (the launches would cost more
-// than they save: 1003 x 3001, 5%: 0.36 against 0.50 ms), and so is a layer of less
-// than one panel, 16 rows (8 x 4096 from rounded weights: 17% move, 0.84 against 0.55
-// ms, and ten sweeps 6.9 against 6.0 ms).
-int cd_rows_limit(int64_t q, int64_t p, bool warm)
+// columns of the blocked form.  A layer of less than one panel, 16 rows, is always taken
+// row by row (8 x 4096 from rounded weights: 17% move, 0.84 against 0.55 ms, and ten
+// sweeps 6.9 against 6.0 ms).
+int cd_rows_limit(int64_t q, int64_t p)
 {
-    const double work = (double)q * (double)p * (double)p;
-    const double bw = 4.0 * (double)p * (double)p <= 2.0e8 ? 9.0e12 : 7.0e12;
-    const double dense = std::max(2.0 * work / 135.0e12, (double)(cdiv(p, 256) + 1) * 50.0e-6);
-    double f = dense * bw / (4.0 * work);
-    if (f > 0.12) {
-        if (!warm || q < 16) return -1;
+    double f = rows_line(q, p);
+    if (f > kFewRows) {
+        if (q < 16) return -1;
         const double move = p <= kOneWave ? 0.45e-6 : 0.87e-6;
         f = std::min(f, ((double)cdiv(p, 256) * 38.0e-6 - 20.0e-6) / ((double)p * move));
         if (f >= 1.0) return -1;
     }
     return (int)(f * (double)std::min<int64_t>(q, kSampleRows) * (double)p);
+}
+
+// The sweeps from What = W on (the first counted) up to which the choice is offered.
+// The first leaves few codes to move: 10 to 40% move in the second, 4 to 16% in the third,
+// 1 to 5% in the fifth, on every layer, bit width and conditioning tried, and from there on
+// the row form took at most 1.15 times the blocked sweep (large layers: the line lies
+// lower, and the launches weigh less).  Where rows are few the row form loses in the second
+// sweep only (layers of as many tokens as channels, 1152 x 1664: 41.6%, 0.79 against 0.26
+// ms; third 16%, 0.35; fourth 8%, 0.20), and the empty launches of one optional sweep
+// cost up to 5% of a call that did not need them (1003 x 3001, 4.5%: 0.23 against 0.50 ms
+// and 0.05 for the launches).  One wave per row loses less (1152 x 1024, 38%: 0.25
+// against 0.16 ms) and gains it back in the next sweeps: nothing is offered.
+int cd_rows_offered(int64_t q, int64_t p)
+{
+    if ((double)q * (double)p * (double)p >= kManyWork) return 8;
+    if (rows_line(q, p) <= kFewRows) return 4;
+    return p > kOneWave ? 2 : 1;
 }
 
 qe_status launch_cd_sample(const float* R, const float* Wh, const float* inv_d, const float* scale,

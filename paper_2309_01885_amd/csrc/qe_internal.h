@@ -476,7 +476,8 @@ qe_status launch_cd(const float* W, const float* Sigma, int64_t q, int64_t p, in
 // counted, from bit 40 on, and their moves) and the first sweep that does (device memory).
 struct RowsChoice { unsigned long long count; int first; };
 bool cd_rows_fits(int64_t q, int64_t p);
-int cd_rows_limit(int64_t q, int64_t p, bool warm);
+int cd_rows_limit(int64_t q, int64_t p);
+int cd_rows_offered(int64_t q, int64_t p);
 qe_status launch_cd_sample(const float* R, const float* Wh, const float* inv_d, const float* scale,
                            const float* zero, const float* inv_s, int64_t q, int64_t p, float maxq,
                            int k, int limit, RowsChoice* choice, const int* status, hipStream_t s);

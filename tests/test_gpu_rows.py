@@ -88,13 +88,15 @@ def test_warm_start_that_keeps_moving(qe, oracle, q, p):
     assert one["obj"] == g["obj"] == want["obj"]
 
 
-def few_tokens(p, n, seed):
-    """Damped Gram matrix of n random tokens, exactly symmetric (on the device): the fewer
-    tokens per channel, the more codes a sweep moves."""
+def few_tokens(p, n, seed, out=0):
+    """Damped Gram matrix of n random tokens, exactly symmetric (on the device), the first
+    `out` channels 30 times as large: the fewer tokens per channel and the more such
+    channels, the more codes a sweep moves."""
     X = dev(synth.gaussian((p, n), seed=seed))
+    X[:out] *= 30
     S = X @ X.T / n
     S = (S + S.T) / 2
-    S.diagonal().add_(0.01)
+    S.diagonal().add_(0.01 * S.diagonal().mean())
     return S.contiguous()
 
 
@@ -116,6 +118,24 @@ def test_few_rows_round_as_many(qe, q, p):
     assert 16 < moves < 0.1 * p, moves               # lists of many moves, below the line
     for a, b in zip(few, (Wh, codes, R)):
         assert torch.equal(a, b[:n])
+
+
+@pytest.mark.parametrize("q,p", [(70, 1501), (384, 1792)])
+def test_few_rows_choose_their_second_sweep(qe, q, p):
+    """As many tokens as channels, some of them large: the second sweep from What = W moves far more codes than
+    the row form is given, also in a layer of few rows.  It runs in the blocked form, the
+    third one row by row.  (QE_RELAX_PERIOD keeps a call in the blocked form.)"""
+    W, S = dev(synth.gaussian((q, p), seed=61, std=0.02)), few_tokens(p, p, 62, out=p // 50)
+    scale, zero = qe.grid_minmax(W, 4)
+
+    def run(sweeps, extra=0):
+        Wh, R, codes = torch.empty_like(W), torch.empty_like(W), torch.zeros((q, p), dtype=torch.uint8, device="cuda")
+        qe.cd_sweep(W, S, 4, scale, zero, Wh, codes, R, sweeps, flags=qe.QE_INIT_FROM_W | extra)
+        return codes, R
+    one, two = run(1), run(2)
+    assert float((one[0] != two[0]).float().mean()) > 0.2
+    assert torch.equal(two[1], run(2, qe.QE_RELAX_PERIOD(255))[1])
+    assert not torch.equal(run(3)[1], run(3, qe.QE_RELAX_PERIOD(255))[1])
 
 
 def test_fixed_point_and_no_objective(qe, oracle):
