@@ -379,12 +379,19 @@ constexpr int kSampleRows = 256;
 // Layers of few rows apply another wave's moves four at a time: nothing but the loads in
 // flight hides the latency of a row of Sigma there (384 x 1792, five sweeps of a layer of
 // 1472 tokens: 1.73 -> 1.65 ms, 1003 x 3001, rho = 0.9, ten sweeps 1.84 -> 1.67, 300 x 6000
-// 2.74 -> 2.58).  That takes 125 registers, four waves per SIMD; where the workgroups then
-// no longer fit the chip at once, more waves hide it better (1282 x 3000 1.36 against
-// 1.53 ms, 768 x 5000, whose five waves load the SIMDs unevenly, 2.72 against 3.11).
-constexpr int kCus = 256, kAheadWavesPerSimd = 4;
+// 2.74 -> 2.58, 1280 x 3000 1.35 -> 1.30).  That takes 125 registers, four waves per SIMD;
+// where the workgroups then no longer fit the chip at once, more waves hide it better (1282
+// x 3000 1.36 against 1.53 ms).  More than four waves load the SIMDs unevenly (768 x 5000
+// 2.72 against 3.11 ms): there each SIMD counts as many as the fullest one.
+constexpr int64_t kCus = 256, kAheadWaves = 16;
 
 static int rows_threads(int64_t p) { return p <= kOneWave ? 64 : (int)(64 * cdiv(p, 1024)); }
+
+static bool rows_ahead(int64_t q, int64_t p)
+{
+    const int64_t waves = rows_threads(p) / 64;
+    return q <= kCus * (kAheadWaves / (waves <= 4 ? waves : 4 * cdiv(waves, (int64_t)4)));
+}
 
 bool cd_rows_fits(int64_t q, int64_t p) { return p <= kRowsMaxP && q <= max_grid(rows_threads(p)); }
 
@@ -475,7 +482,7 @@ qe_status launch_cd_rows(const float* Sigma, int64_t q, int64_t p, const float* 
         if (p <= 256) QE_ROWS(1, false, false);
         else if (p <= 512) QE_ROWS(2, false, false);
         else if (p <= kOneWave) QE_ROWS(4, false, false);
-        else if (q <= kCus * (kAheadWavesPerSimd / cdiv(rows_threads(p), 256))) QE_ROWS(4, true, true);
+        else if (rows_ahead(q, p)) QE_ROWS(4, true, true);
         else QE_ROWS(4, true, false);
 #undef QE_ROWS
         if (obj)

@@ -100,7 +100,7 @@ def few_tokens(p, n, seed, out=0):
     return S.contiguous()
 
 
-@pytest.mark.parametrize("q,p", [(1030, 1101), (1030, 2304), (1030, 3075), (520, 4100)])
+@pytest.mark.parametrize("q,p", [(2060, 1101), (1290, 2304), (1030, 3075), (520, 4100)])
 def test_few_rows_round_as_many(qe, q, p):
     """Rows are independent: those of a layer small enough to apply another wave's moves
     several at a time end bit for bit as within a layer that applies them one by one."""
