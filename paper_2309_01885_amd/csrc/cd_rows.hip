@@ -23,9 +23,9 @@
 // 0.1% the launch's own reads and writes of R, What and the codes remain (0.11
 // ms at 4096 x 4096, paid once per launch and not per sweep).  The blocked sweep
 // takes 0.4 to 1.1 ms there and 2.2 to 6.9 ms at 4096 x 11008.  Ten sweeps from
-// What = W: 8.1 -> 3.25 ms (4096 x 4096), 45.7 -> 19.8 ms (4096 x 11008), 26.3
-// -> 14.6 ms (11008 x 4096), 8.7 -> 2.6 ms (1003 x 3001).
-// 1024 columns per wave keep a lane's state (16 values of R, 16 codes) at 79
+// What = W: 8.06 -> 3.04 ms (4096 x 4096), 45.4 -> 20.0 ms (4096 x 11008), 26.7
+// -> 14.7 ms (11008 x 4096), 8.69 -> 2.05 ms (1003 x 3001).
+// 1024 columns per wave keep a lane's state (16 values of R, 16 codes) at 78
 // registers: six waves per SIMD, which hide the latency of the serial search of
 // one row behind the other rows.  Turns of 256 columns in place of 1024 (more
 // barriers, more reuse of Sigma rows in L2) took 10 to 30% longer, and 8 waves

@@ -509,7 +509,7 @@ __global__ __launch_bounds__(256) void power_last_kernel(const double* part, int
 // kernel, where every word is there before it is read: the same sums in the same order,
 // so the result does not depend on what else the device was doing.
 // Bound by the exchange of y (about 2.7 us an iteration) and, at 4096, by the
-// conversions of the fp64 products: 12.7 -> 6.4 us an iteration at 4096 (Sigma, 67 MB,
+// conversions of the fp64 products: 12.7 -> 5.5 us an iteration at 4096 (Sigma, 67 MB,
 // streamed before), 6.7 -> 2.0 us at 1025, the call 5.0 -> 2.5 ms and 3.2 -> 1.0 ms.
 constexpr int64_t kChipMaxP = 4096;          // 256 workgroups of 128 values per lane
 
